@@ -1,0 +1,352 @@
+"""The workloads that this framework's speed is judged by.
+
+Each case is one call, or one training step, of the TT-embedding gather through the public
+Python entry points (TTEmbedding, TTEmbeddingBag): look-ups for serving, pooled bags, and
+training with gradients or with the fused SGD step; three cores as well as two, four and five;
+ranks 8 to 64 and rows of 16 to 128 columns; batches from a few thousand indices to 5.2 million.
+
+listed() names the fixed cases, draw() gives others of the same ranges, prepare() makes what a
+user's program holds before the call, run() is one pass, work() the least bytes and flops that
+pass needs, tolerance() how far another correct float32 implementation may be off, and exact()
+the result in 64 bits by plain torch.
+"""
+from __future__ import annotations
+
+import math
+
+import numpy as np
+import torch
+
+import paper_2609_03459_amd as tt
+
+LR = 0.01
+
+
+def _case(name, mode, tables, rows, dims, rank, batch, bags, dist, alpha=0.0, sigma=0.05):
+    """rows, dims: the factors of the row count and of the row length, as 'a,b,c'.
+
+    mode  'forward': the pooled (or plain) lookup alone
+          'grad'   : lookup, then the gradients of every core through autograd
+          'step'   : lookup, then the training step without autograd (cores updated in place)
+    bags  'single' (one index per bag, no offsets), 'fixedK', or 'poissonK' clipped to [1, 64]
+    dist  'uniform', 'zipf' over a random permutation of the rows, or 'hotprefix': half of the
+          lookups on 1% of the (i1, i2) prefixes, the rest zipf
+    """
+    return dict(name=name, mode=mode, tables=tables, rows=rows, dims=dims, rank=rank, batch=batch, bags=bags,
+                dist=dist, alpha=alpha, sigma=sigma)
+
+
+def listed():
+    return [
+        # a small online lookup: one table of a million rows, one request batch, latency-bound
+        _case("lookup_1e6_d16_r8", "forward", 1, "100,100,100", "2,2,4", 8, 4096, "single", "uniform", sigma=0.1),
+        # the large-batch plain lookup of one 1e7-row table with popular rows
+        _case("lookup_1e7_d64_r16", "forward", 1, "200,200,250", "4,4,4", 16, 32768, "single", "zipf", 1.05),
+        # inference of a recommendation model's eight sparse features, sum-pooled multi-hot bags
+        _case("pooled_8x1e7_d128_r32", "forward", 8, "200,200,250", "4,4,8", 32, 32768, "poisson20", "zipf", 1.1),
+        # the same model's training step with the fused SGD update: the framework's main workload
+        _case("train_8x1e7_d128_r32", "step", 8, "200,200,250", "4,4,8", 32, 32768, "poisson20", "zipf", 1.1),
+        # the narrow rows the FlowTT paper trains (D = 32, R = 32), gradients handed to an optimizer
+        _case("train_8x1e7_d32_r32", "grad", 8, "200,200,250", "4,4,2", 32, 32768, "poisson20", "zipf", 1.1),
+        # one very large table whose load sits on few prefixes, as in a click log: serving
+        _case("hot_1e8_d128_r64", "forward", 1, "400,500,500", "4,4,8", 64, 32768, "fixed32", "hotprefix", 1.2),
+        # and training that table
+        _case("train_hot_1e8_d128_r64", "grad", 1, "400,500,500", "4,4,8", 64, 32768, "fixed32", "hotprefix", 1.2),
+        # a mid-sized model at a small rank, the usual compression point of TT embeddings
+        _case("train_4x1e7_d64_r16", "grad", 4, "200,200,250", "4,4,4", 16, 8192, "poisson20", "zipf", 1.05),
+        # four cores: the same 1e7-row tables, compressed one level further
+        _case("train_4x1e7_4cores_d128_r32", "step", 4, "20,10,200,250", "2,2,4,8", 32, 16384, "poisson20", "zipf",
+              1.1),
+        # two cores, the low-rank factorisation of a table
+        _case("train_2x1e7_2cores_d128_r32", "grad", 2, "4000,2500", "16,8", 32, 8192, "poisson20", "zipf", 1.1),
+        # fine-tuning on a small batch: odd sizes, launches and host work count
+        _case("train_3x2e5_d32_r32_small", "grad", 3, "61,59,57", "4,4,2", 32, 257, "poisson20", "zipf", 1.1),
+        # factors nobody rounded: D = 60 = 3*4*5, rank 12
+        _case("train_5x4e5_d60_r12_odd", "grad", 5, "37,91,113", "3,4,5", 12, 1111, "poisson10", "uniform"),
+    ]
+
+
+# Shapes of the drawn cases: (row-length factors, ranks, most lookups of one pass).  The lookups
+# are bounded so that no drawn case takes longer than the largest listed one.
+_SHAPES = [
+    ((2, 2, 4), (4, 8, 16), 1 << 18),
+    ((4, 4, 2), (16, 32), 1 << 18),
+    ((4, 4, 2), (32,), 1 << 21),
+    ((4, 4, 4), (8, 16, 32), 1 << 17),
+    ((4, 4, 8), (32,), 1 << 21),
+    ((4, 4, 8), (64,), 1 << 19),
+    ((4, 4, 8), (16,), 1 << 17),
+    ((3, 4, 5), (12, 20), 1 << 16),
+    ((2, 2, 4, 8), (32,), 1 << 19),
+    ((2, 2, 2, 4), (16,), 1 << 17),
+    ((2, 2, 1, 4, 8), (32,), 1 << 19),
+    ((16, 8), (16, 32), 1 << 18),
+]
+
+
+def _log_int(rng, lo, hi):
+    return int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+
+
+def draw(rng):
+    dims, ranks, most = rng.choice(_SHAPES)
+    rank = rng.choice(ranks)
+    L = len(dims)
+    mode = rng.choice(["forward", "grad", "step"])
+    tables = rng.choice([1, 1, 2, 3, 4, 6, 8])
+    total = _log_int(rng, 1e5, 2e7)
+    if L == 2:
+        a = max(2, int(round(math.sqrt(total) * rng.uniform(0.7, 1.6))))
+        rows = (a, max(2, min(total // a, 4000)))
+    else:
+        last = rng.randint(40, 250)
+        mid = rng.randint(40, 220)
+        first = max(2, min(int(round(total / (last * mid))), 450))
+        if L == 3:
+            rows = (first, mid, last)
+        else:  # the leading cores share the first factor
+            k = L - 2
+            r = first ** (1.0 / k)
+            lead = [max(2, int(round(r * rng.uniform(0.7, 1.4)))) for _ in range(k)]
+            rows = tuple(lead) + (mid, last)
+    kind = rng.choice(["single", "fixed", "poisson", "poisson"])
+    mean = 1 if kind == "single" else rng.randint(2, 40)
+    batch = _log_int(rng, 200, 33000)
+    batch = max(64, min(batch, most // (tables * mean)))
+    if rng.random() < 0.7:
+        batch |= 1
+    dist = rng.choice(["uniform", "zipf", "zipf"])
+    alpha = round(rng.uniform(1.02, 1.25), 3) if dist == "zipf" else 0.0
+    c = _case("", mode, tables, ",".join(map(str, rows)), ",".join(map(str, dims)), rank, batch,
+              kind if kind == "single" else f"{kind}{mean}", dist, alpha, 0.05 if rank >= 16 else 0.1)
+    del c["name"]
+    return c
+
+
+# ---------------------------------------------------------------------------
+# inputs
+# ---------------------------------------------------------------------------
+def _factors(case):
+    return tuple(int(x) for x in case["rows"].split(",")), tuple(int(x) for x in case["dims"].split(","))
+
+
+def _core_shapes(case):
+    n, d = _factors(case)
+    T, R, L = case["tables"], case["rank"], len(n)
+    return [[T, n[k]] + ([R] if k else []) + [d[k]] + ([R] if k < L - 1 else []) for k in range(L)]
+
+
+def _zipf(alpha, n, size, g, dev):
+    """Ranks 0 .. n-1 with P(k) ~ (k + 1)^-alpha, by inverting the cumulative sum."""
+    cdf = torch.arange(1, n + 1, dtype=torch.float64, device=dev).pow_(-alpha).cumsum_(0)
+    u = torch.rand(size, dtype=torch.float64, device=dev, generator=g) * cdf[-1]
+    return torch.searchsorted(cdf, u).clamp_(max=n - 1)
+
+
+def _indices(case, m, g, dev):
+    n, _ = _factors(case)
+    N = math.prod(n)
+    if case["dist"] == "uniform":
+        return torch.randint(0, N, (m,), dtype=torch.int64, device=dev, generator=g)
+    if case["dist"] == "zipf":
+        perm = torch.randperm(N, device=dev, generator=g)
+        return perm[_zipf(case["alpha"], N, m, g, dev)]
+    block = n[-1]
+    nblk = N // block
+    nhot = max(1, nblk // 100)
+    hot_blocks = torch.randperm(nblk, device=dev, generator=g)[:nhot]
+    hot = hot_blocks[_zipf(case["alpha"], nhot, m, g, dev)] * block + torch.randint(
+        0, block, (m,), device=dev, generator=g)
+    perm = torch.randperm(N, device=dev, generator=g)
+    cold = perm[_zipf(case["alpha"], N, m, g, dev)]
+    return torch.where(torch.rand(m, device=dev, generator=g) < 0.5, hot, cold)
+
+
+def _inputs(case, seed, dev="cuda"):
+    """Cores, indices, offsets (None for single-index bags) and, for training, the upstream gradient."""
+    g = torch.Generator(device=dev)
+    g.manual_seed(int(seed))
+    T, B = case["tables"], case["batch"]
+    cores = [torch.randn(s, generator=g, dtype=torch.float32, device=dev) * case["sigma"] for s in _core_shapes(case)]
+    kind = case["bags"]
+    if kind == "single":
+        lens = None
+        counts = [B] * T
+    elif kind.startswith("fixed"):
+        lens = torch.full((T, B), int(kind[5:]), dtype=torch.int64, device=dev)
+        counts = [B * int(kind[5:])] * T
+    else:
+        lens = torch.poisson(torch.full((T, B), float(kind[7:]), device=dev), generator=g).clamp_(1, 64).long()
+        counts = lens.sum(1).tolist()
+    idx = torch.cat([_indices(case, m, g, dev) for m in counts])
+    offsets = None
+    if lens is not None:
+        offsets = torch.zeros(T * B + 1, dtype=torch.int64, device=dev)
+        offsets[1:] = lens.flatten().cumsum(0)
+    dV = None
+    if case["mode"] != "forward":
+        D = math.prod(_factors(case)[1])
+        dV = torch.randn((T, B, D), generator=g, dtype=torch.float32, device=dev)
+    return cores, idx, offsets, dV
+
+
+def prepare(case, seed):
+    n, d = _factors(case)
+    cores, idx, offsets, dV = _inputs(case, seed)
+    bag = tt.TTEmbeddingBag(case["tables"], math.prod(n), n, d, case["rank"], max_indices=idx.numel(),
+                            max_bags=case["batch"])
+    with torch.no_grad():
+        for p, c in zip(bag.cores, cores):
+            p.copy_(c)
+    return dict(mode=case["mode"], bag=bag, idx=idx, offsets=offsets, dV=dV)
+
+
+def run(state):
+    bag, idx, offsets, dV = state["bag"], state["idx"], state["offsets"], state["dV"]
+    if state["mode"] == "forward":
+        with torch.no_grad():
+            return bag(idx, offsets)
+    if state["mode"] == "grad":
+        out = bag(idx, offsets)
+        return (out, *torch.autograd.grad(out, bag.cores, dV))
+    with torch.no_grad():
+        out = bag(idx, offsets)
+        bag.step_fused(idx, offsets, dV, LR)
+    return (out, *[p.detach() for p in bag.cores])
+
+
+# ---------------------------------------------------------------------------
+# least work
+# ---------------------------------------------------------------------------
+def _distinct(n_bins, draws):
+    return n_bins * -math.expm1(draws * math.log1p(-1.0 / n_bins)) if n_bins > 1 else float(draws > 0)
+
+
+def _zipf_distinct(alpha, n, m):
+    """Expected distinct ranks of m zipf draws, summed over ranks (in log-spaced bins past 1e5)."""
+    head = min(n, 100000)
+    k = np.arange(1, head + 1, dtype=np.float64)
+    width = np.ones(head)
+    if n > head:
+        edges = np.unique(np.floor(np.geomspace(head + 1, n + 1, 4000)))
+        k = np.concatenate([k, 0.5 * (edges[:-1] + edges[1:] - 1)])
+        width = np.concatenate([width, np.diff(edges)])
+    w = k ** -alpha
+    p = w / (w * width).sum()
+    return float((width * -np.expm1(m * np.log1p(-np.minimum(p, 0.999999)))).sum())
+
+
+def _distinct_rows(case, m):
+    """Expected distinct rows and prefixes of one table's m lookups."""
+    n, _ = _factors(case)
+    N = math.prod(n)
+    P = N // n[-1]
+    if case["dist"] == "uniform":
+        U = _distinct(N, m)
+        return U, _distinct(P, U)
+    if case["dist"] == "zipf":
+        U = _zipf_distinct(case["alpha"], N, m)
+        return U, _distinct(P, U)
+    nhot = max(1, P // 100)
+    k = np.arange(1, nhot + 1, dtype=np.float64) ** -case["alpha"]
+    per = 0.5 * m * k / k.sum()
+    hot = float((n[-1] * -np.expm1(per * math.log1p(-1.0 / n[-1]))).sum())
+    cold = _zipf_distinct(case["alpha"], N, 0.5 * m)
+    return hot + cold, float(-np.expm1(-per).sum()) + _distinct(P, cold)
+
+
+def work(case):
+    n, d = _factors(case)
+    T, B, R, L = case["tables"], case["batch"], case["rank"], len(n)
+    D = math.prod(d)
+    kind = case["bags"]
+    mean = 1 if kind == "single" else int(kind[5:] if kind.startswith("fixed") else kind[7:])
+    M = B * mean  # lookups of one table
+    U, P = _distinct_rows(case, M)
+    if L == 2:
+        fwd = U * 2.0 * D * R
+        bwd = U * 4.0 * D * R
+        chain = 0.0
+    else:
+        d1 = math.prod(d[:L - 2])
+        fwd = P * 2.0 * d1 * d[-2] * R * R + U * 2.0 * D * R
+        bwd = P * 6.0 * d1 * d[-2] * R * R + U * 4.0 * D * R
+        chain, m, rows = 0.0, d[0], n[0]
+        for k in range(1, L - 2):
+            rows *= n[k]
+            chain += rows * 2.0 * m * R * d[k] * R
+            m *= d[k]
+    cores = sum(math.prod(s) for s in _core_shapes(case)) * 4.0
+    index = 8.0 * T * M + (0.0 if kind == "single" else 8.0 * (T * B + 1))
+    out = 4.0 * T * B * D
+    flops = T * (fwd + chain) + T * M * D * (1.0 if kind != "single" else 0.0)
+    nbytes = cores + index + out
+    if case["mode"] != "forward":
+        flops += T * (bwd + 2.0 * chain) + T * M * D
+        nbytes += out + cores
+    return {"bytes": nbytes, "flops": flops}
+
+
+def tolerance(case):
+    # measured against exact() over these cases and a dozen drawn ones: at most 6.6e-7 and 3.4e-5
+    return {"rel": 2.5e-6, "max": 1.4e-4}
+
+
+# ---------------------------------------------------------------------------
+# the result in 64 bits
+# ---------------------------------------------------------------------------
+def exact(case, seed):
+    cores, idx, offsets, dV = _inputs(case, seed)
+    n, d = _factors(case)
+    T, B, R, L = case["tables"], case["batch"], case["rank"], len(n)
+    D = math.prod(d)
+    N = math.prod(n)
+    dev = idx.device
+    cores64 = [c.double() for c in cores]
+    # bag and table of every lookup, then the distinct (table, row) pairs
+    if offsets is None:
+        bag = torch.arange(T * B, device=dev)
+    else:
+        bag = torch.repeat_interleave(torch.arange(T * B, device=dev), offsets[1:] - offsets[:-1])
+    key, inv = torch.unique((bag // B) * N + idx, return_inverse=True)
+    t, g = key // N, key % N
+    digits = []
+    for k in reversed(range(L)):
+        digits.insert(0, t * n[k] + g % n[k])
+        g = g // n[k]
+    flat = [c.reshape(T * n[k], *((R,) if k else (1,)), -1) for k, c in enumerate(cores64)]  # [T n_k][r_k][d_k r_{k+1}]
+    U = key.numel()
+    grads = None
+    out = torch.zeros((T * B, D), dtype=torch.float64, device=dev)
+    if case["mode"] != "forward":
+        grads = [torch.zeros_like(f) for f in flat]
+        dE = torch.zeros((U, D), dtype=torch.float64, device=dev)
+        dV64 = dV.double().reshape(T * B, D)
+        for a in range(0, idx.numel(), 1 << 20):
+            dE.index_add_(0, inv[a:a + (1 << 20)], dV64[bag[a:a + (1 << 20)]])
+    E = torch.empty((U, D), dtype=torch.float64, device=dev)
+    step = max(256, (1 << 27) // max(f.shape[1] * f.shape[2] for f in flat))
+    for a in range(0, U, step):
+        sl = [digits[k][a:a + step] for k in range(L)]
+        S = [flat[k][sl[k]] for k in range(L)]
+        X = [S[0].reshape(len(S[0]), d[0], R)]
+        for k in range(1, L):
+            r = R if k < L - 1 else 1
+            X.append(torch.bmm(X[-1], S[k]).reshape(len(S[0]), -1, r))
+        E[a:a + step] = X[-1].reshape(len(S[0]), D)
+        if grads is not None:
+            dX = dE[a:a + step].reshape(len(S[0]), -1, 1)
+            for k in range(L - 1, 0, -1):
+                dX = dX.reshape(len(S[0]), X[k - 1].shape[1], -1)
+                grads[k].index_add_(0, sl[k], torch.bmm(X[k - 1].transpose(1, 2).contiguous(), dX))
+                dX = torch.bmm(dX, S[k].transpose(1, 2).contiguous())
+            grads[0].index_add_(0, sl[0], dX.reshape(len(S[0]), 1, -1))
+    for a in range(0, idx.numel(), 1 << 20):
+        out.index_add_(0, bag[a:a + (1 << 20)], E[inv[a:a + (1 << 20)]])
+    out = out.reshape(T, B, D)
+    if grads is None:
+        return out
+    grads = [gk.reshape(c.shape) for gk, c in zip(grads, cores64)]
+    if case["mode"] == "grad":
+        return (out, *grads)
+    return (out, *[c - LR * gk for c, gk in zip(cores64, grads)])
