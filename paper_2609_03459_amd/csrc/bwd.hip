@@ -494,7 +494,7 @@ __global__ void __launch_bounds__(BWD_THREADS) k_bwd_generic(ShapeArgs s, const 
   __shared__ int s_chunk, s_flag;
   const int nsl = ctr[C_NSLICES];
   const int nchunks = (int)run_base[s.T * s.n2];
-  int victim = 0;
+  Worker worker = make_worker(SCHED_NQ, 1, 0);
   int next = share_lo(nchunks, (int)gridDim.x, (int)blockIdx.x);
   int cur_pg = -1;
   const int rows12 = s.d1 * s.d2;
@@ -505,8 +505,7 @@ __global__ void __launch_bounds__(BWD_THREADS) k_bwd_generic(ShapeArgs s, const 
   const int RD = s.R * s.d3;
   const int g_dd = RD >= BWD_THREADS ? 1 : (BWD_THREADS / RD < SLICE_ROWS ? BWD_THREADS / RD : SLICE_ROWS);
   while (true) {
-    const int c = claim_block_sched(s.sched, ctr + C_BWD_CTR, nchunks, blockIdx.x % SCHED_NQ, &victim, &s_chunk,
-                                    &next);
+    const int c = claim_block_sched(s.sched, ctr + C_BWD_CTR, nchunks, &worker, &s_chunk, &next);
     if (c < 0) break;
     const int4 ch = chunks[c];
     const int s0 = ch.x, s1 = ch.x + ch.y;

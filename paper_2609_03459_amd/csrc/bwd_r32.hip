@@ -131,7 +131,8 @@ __global__ void __launch_bounds__(64 * BW_WAVES, 1)
   const float* scr_a = scr + SCR_PITCH * l15 + 16 * l4;
   const buf_t g3buf = make_buf(G3t, (uint32_t)s.n3 * (128u * D3));
 
-  int cursor = 0;
+  // one queue per owner; its workgroups are blocks q, q + nq, ... of the grid
+  Worker worker = {1, 0, wave * (int)(gridDim.x / nq) + (int)(blockIdx.x / nq), (int)(gridDim.x / nq), BW_WAVES, 0, true};
   int cur_run = -1;
   float Bop[32];   // stage-1 B operand B_h[a = 4 s + l4][16 nt + l15], (s, nt) -> 4 s + nt
   float BTop[32];  // dA B operand B_h^T[(j2 = l4, b' = s)][a = 16 nt2 + l15], (s, nt2) -> 16 nt2 + s
@@ -255,7 +256,7 @@ __global__ void __launch_bounds__(64 * BW_WAVES, 1)
   int st_next = share_lo(nch, onw, owid);
   const int st_hi = share_lo(nch, onw, owid + 1);
   auto next_chunk = [&]() {
-    const int cc = sched_static(s.sched) ? (st_next < st_hi ? st_next++ : -1) : claim_queues(qctr, nch, 1, 0, &cursor);
+    const int cc = sched_static(s.sched) ? (st_next < st_hi ? st_next++ : -1) : claim_queues(qctr, nch, &worker);
     if (cc >= 0) {
       const int4 ch = chunks[c_lo + cc];
       f = __builtin_amdgcn_readfirstlane(ch.x);

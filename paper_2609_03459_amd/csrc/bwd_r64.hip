@@ -59,7 +59,7 @@ __global__ void __launch_bounds__(64 * B64_WAVES, B64_WG_PER_CU)
   // LDS tile: stage-1 write of (slice l4, row 4 r + j2, column b = 16 (nt & 3) + l15)
   const int wr_base = l4 * B64_SLICE + l15;
 
-  int cursor = 0;
+  Worker worker = make_worker(SCHED_NQ, B64_WAVES, wave);
   const int wid = blockIdx.x * B64_WAVES + wave, nw = gridDim.x * B64_WAVES;
   int st_next = share_lo(nch, nw, wid);
   const int st_hi = share_lo(nch, nw, wid + 1);
@@ -68,7 +68,7 @@ __global__ void __launch_bounds__(64 * B64_WAVES, B64_WG_PER_CU)
     if (sched_static(s.sched))
       c = st_next < st_hi ? st_next++ : -1;
     else
-      c = claim_queues(ctr + C_BWD_CTR, nch, SCHED_NQ, blockIdx.x % SCHED_NQ, &cursor);
+      c = claim_queues(ctr + C_BWD_CTR, nch, &worker);
     if (c < 0) break;
     const int4 ch = chunks[c];
     const int f = __builtin_amdgcn_readfirstlane(ch.x);

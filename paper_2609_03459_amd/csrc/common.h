@@ -277,39 +277,68 @@ __device__ __forceinline__ float2 ntl2(const float2* p) {
 // Persistent-thread scheduler with chunked work stealing (FlowTT Section 3.4).
 // The chunk list is cut into nq contiguous queues; queue v holds chunks
 // [share_lo(v), share_lo(v + 1)) and has one claim counter on a 128-byte line
-// of its own.  A worker claims the next chunk of its home queue with a single
-// atomic (consecutive chunks, so neighbouring groups stay in the home XCD's L2);
-// once the home queue is empty it steals from the following queues in turn.  An
-// empty queue is never visited again, so a worker makes at most nq failed
-// claims before it exits.  The forward uses one queue per XCD (workgroup
-// blockIdx % 8 runs on XCD blockIdx % 8); the specialised backward gives every
-// (table, rank half) owner one queue, since its LDS accumulator is its own.
+// of its own.  A worker takes one chunk of its home queue by its rank there, without
+// an atomic, then claims the following ones with a single atomic each (consecutive
+// chunks, so neighbouring groups stay in the home XCD's L2); once the home queue is
+// empty it steals from the following queues in turn.  An empty queue is never visited
+// again, and one that was dealt out by rank never asked, so a worker makes at most nq
+// failed claims before it exits, and none in a launch with no more chunks than workers.
+// The forward uses one queue per XCD (workgroup blockIdx % 8 runs on XCD blockIdx % 8); the specialised backward
+// gives every (table, rank half) owner one queue, since its LDS accumulator is its own.
+//
+// The claims of thousands of workers on eight lines are what a small launch waits for: with
+// every chunk claimed and eight failed claims per worker, the d = (4, 4, 2), R = 32 forward
+// over 15,000 indices took 68 us; by rank it takes 33 us.  (Looking at the counters with
+// plain loads before a steal, instead of failed claims, cost the large launches 25 us.)
 constexpr int SCHED_NQ = 8;       // queues of the forward scheduler: one per XCD
 constexpr int SCHED_STRIDE = 32;  // ints between queue counters (128 bytes)
 
 __device__ __forceinline__ int share_lo(int nchunks, int W, int v) { return (int)(((int64_t)nchunks * v) / W); }
 
-__device__ __forceinline__ int claim_queues(int32_t* q, int nchunks, int nq, int home, int* cursor) {
-  while (*cursor < nq) {
-    int v = home + *cursor;
-    if (v >= nq) v -= nq;
-    const int lo = share_lo(nchunks, nq, v), hi = share_lo(nchunks, nq, v + 1);
-    int c = -1;
-    if (lane_id() == 0) {
-      const int got = atomicAdd(&q[v * SCHED_STRIDE], 1);
-      if (lo + got < hi) c = lo + got;
+// A worker's place in the queues: nq queues; its home and rank there; how many queues it
+// has left behind; the workers whose home is queue v, which took its first chunks by rank:
+// blocks v, v + nq, ... of nb, `per` workers each.  Ranks go through the blocks first, so
+// that few chunks spread over as many CUs as there are.
+struct Worker {
+  int nq, home, rank, nb, per, cursor;
+  bool fresh;  // the chunk by rank is still to be taken
+};
+__device__ __forceinline__ int queue_blocks(int nb, int nq, int v) { return nb > v ? (nb - 1 - v) / nq + 1 : 0; }
+__device__ __forceinline__ Worker make_worker(int nq, int per, int w) {
+  const int home = (int)blockIdx.x % nq;
+  return Worker{nq, home, w * queue_blocks((int)gridDim.x, nq, home) + (int)blockIdx.x / nq, (int)gridDim.x, per, 0, true};
+}
+
+__device__ __forceinline__ int claim_queues(int32_t* q, int nchunks, Worker* k) {
+  while (k->cursor < k->nq) {
+    int v = k->home + k->cursor;
+    if (v >= k->nq) v -= k->nq;
+    const int hi = share_lo(nchunks, k->nq, v + 1);
+    if (k->fresh) {  // v is the home queue
+      k->fresh = false;
+      const int c = share_lo(nchunks, k->nq, v) + k->rank;
+      if (c < hi) return c;
+    } else {
+      const int lo = share_lo(nchunks, k->nq, v) + queue_blocks(k->nb, k->nq, v) * k->per;
+      if (lo < hi) {
+        int c = -1;
+        if (lane_id() == 0) {
+          const int got = lo + atomicAdd(&q[v * SCHED_STRIDE], 1);
+          if (got < hi) c = got;
+        }
+        c = __builtin_amdgcn_readfirstlane(c);
+        if (c >= 0) return c;
+      }
     }
-    c = __builtin_amdgcn_readfirstlane(c);
-    if (c >= 0) return c;
-    ++*cursor;
+    ++k->cursor;
   }
   return -1;
 }
 
 // Block-level worker: wave 0 claims for the block.
-__device__ __forceinline__ int claim_block(int32_t* q, int nchunks, int nq, int home, int* cursor, int* s_chunk) {
+__device__ __forceinline__ int claim_block(int32_t* q, int nchunks, Worker* k, int* s_chunk) {
   if (threadIdx.x < 64) {
-    const int c = claim_queues(q, nchunks, nq, home, cursor);
+    const int c = claim_queues(q, nchunks, k);
     if (threadIdx.x == 0) *s_chunk = c;
   }
   __syncthreads();
@@ -335,13 +364,13 @@ constexpr int CKPT_SLOTS = 1024;
 // (SCHED_STATIC; *next starts at the share's first chunk), or from the shared
 // queues with stealing.  `sched` is a kernel argument, so every thread of the
 // block takes the same branch.
-__device__ __forceinline__ int claim_block_sched(int sched, int32_t* q, int nchunks, int home, int* cursor,
-                                                 int* s_chunk, int* next) {
+__device__ __forceinline__ int claim_block_sched(int sched, int32_t* q, int nchunks, Worker* k, int* s_chunk,
+                                                 int* next) {
   if (sched_static(sched)) {
     const int hi = share_lo(nchunks, (int)gridDim.x, (int)blockIdx.x + 1);
     return *next < hi ? (*next)++ : -1;
   }
-  return claim_block(q, nchunks, SCHED_NQ, home, cursor, s_chunk);
+  return claim_block(q, nchunks, k, s_chunk);
 }
 
 // Checkpointed intermediates of the generic kernels (Section 3.5).  The entry of

@@ -72,13 +72,12 @@ __global__ void __launch_bounds__(FWD_THREADS) k_fwd_generic(ShapeArgs s, const 
   // work units: FWD_CHUNK consecutive slices, or with SCHED_GROUP the chunk list's whole groups
   const bool by_group = s.sched == SCHED_GROUP;
   const int nchunks = by_group ? (int)run_base[s.T * s.n2] : (nsl + FWD_CHUNK - 1) / FWD_CHUNK;
-  int victim = 0;
+  Worker worker = make_worker(SCHED_NQ, 1, 0);
   int next = share_lo(nchunks, (int)gridDim.x, (int)blockIdx.x);
   int cur_pg = -1, cur_run = -1;
   const float* Bm = G2;
   while (true) {
-    const int c = claim_block_sched(s.sched, ctr + C_FWD_CTR, nchunks, blockIdx.x % SCHED_NQ, &victim, &s_chunk,
-                                    &next);
+    const int c = claim_block_sched(s.sched, ctr + C_FWD_CTR, nchunks, &worker, &s_chunk, &next);
     if (c < 0) break;
     int s0, s1;
     if (by_group) {
@@ -203,7 +202,7 @@ __global__ void __launch_bounds__(64 * F32_WAVES, F32_WG_PER_CU)
   const uint32_t vo_e = D3 == 8 ? 4u * (uint32_t)((l4 >> 1) * 128 + l15 * 8 + 4 * (l4 & 1))
                                 : 4u * (uint32_t)(2 * l4 * DW + l15 * 2);
 
-  int cursor = 0;
+  Worker worker = make_worker(SCHED_NQ, F32_WAVES, wave);
   int cur_run = -1;
   float Bop[64];  // B[a = 4 s + l4][16 nt + l15], (s, nt) -> 8 s + nt
 
@@ -220,7 +219,7 @@ __global__ void __launch_bounds__(64 * F32_WAVES, F32_WG_PER_CU)
     if (sched_static(s.sched))
       c = st_next < st_hi ? st_next++ : -1;
     else
-      c = claim_queues(ctr + C_FWD_CTR, nch, SCHED_NQ, blockIdx.x % SCHED_NQ, &cursor);
+      c = claim_queues(ctr + C_FWD_CTR, nch, &worker);
     qd = 0;
     if (c >= 0) {
       const int4 ch = chunks[c];
@@ -552,7 +551,7 @@ __global__ void __launch_bounds__(64 * F64_WAVES, F64_WG_PER_CU)
   const int wr_base = l4 * F64_SLICE + l15;
   const int rd_base = l15 * F64_PITCH + 16 * l4;
 
-  int cursor = 0;
+  Worker worker = make_worker(SCHED_NQ, F64_WAVES, wave);
   int c_rb = 0, c_nr = 0, c_i1 = 0;
   int f = 0, ns = 0, run = -1, t = 0, qd = 0;
   int c = -1;
@@ -563,7 +562,7 @@ __global__ void __launch_bounds__(64 * F64_WAVES, F64_WG_PER_CU)
     if (sched_static(s.sched))
       c = st_next < st_hi ? st_next++ : -1;
     else
-      c = claim_queues(ctr + C_FWD_CTR, nch, SCHED_NQ, blockIdx.x % SCHED_NQ, &cursor);
+      c = claim_queues(ctr + C_FWD_CTR, nch, &worker);
     qd = 0;
     if (c >= 0) {
       const int4 ch = chunks[c];
