@@ -1,0 +1,802 @@
+// Fused forward and backward for every shape that the kernels specialised for
+// d = (4, 4, 8) and (4, 4, 2) at R = 32 and 64 do not serve (FlowTT Section 3.2,
+// Fig. 3 and Eq. 1), on the matrix cores.
+//
+// A wave works alone, on a stack of slices of one (t, i2) run at a time: as many
+// slices as fill the 16 rows of a matrix tile with their d1 rows of A (SQ = 16 / d1,
+// at least one).  Its LDS tile holds the stack's C, row (slice, j1, j2) of R floats.
+//   stage 1   C (stack rows x d2 R) = A (stack rows x R) . B (R x d2 R), B = G2[t][i2]
+//             read through L2; with two cores (identity middle core) C is A
+//   forward   E^T (items x jj) = D^T (items x R) . C'^T (R x jj) per tile of 16 items
+//             of a slice, an item being one (row, j3), jj = (j1, j2)
+//   backward  dD (items x R) = dE^T (items x jj) . C (jj x R) per tile, and
+//             dC (jj x R) += dE (jj x items) . D (items x R) over a slice's tiles;
+//             the slice's dC replaces its C in the tile, and dA = dC . B^T per stack
+// The backward writes partials only: dD per row, dC and dA per slice; dG2 is formed
+// from the dC of each run by k_dg2_any, and the fixed-order segment sums finish the rest.
+//
+// What bounds these kernels is latency, not the matrix pipe: a tile is a dozen matrix
+// instructions behind a chain of two dependent loads (i3 of a row, then its slice of
+// G3).  Hence one-wave stacks without block barriers, as many waves per CU as the
+// registers allow, and the next tile's operands in flight while a tile is computed.
+// Against the block-per-slice vector-ALU kernels these replaced (they remain for the
+// checkpointed schedule): d = (4, 4, 4), R = 16, 4 tables, 655k look-ups, forward kernel
+// 470 -> 98 us, backward 1,311 -> 137 us; d = (3, 4, 5), R = 12, 55k look-ups, 83 -> 26 and
+// 247 -> 52 us; two cores, d = (16, 8), R = 32, 328k look-ups, 218 -> 31 and 594 -> 55 us.
+#pragma once
+
+#include "common.h"
+
+namespace ttemb {
+
+// Quotients of values below 2^17 by a divisor below 2^13 without a division:
+// floor(x / d) = mulhi(x, ceil(2^32 / d)), exact while x (d - 1) < 2^32; d = 1 has no such
+// magic number and is marked by 0.
+static uint32_t div_magic(uint32_t d) {
+  return d <= 1 ? 0u : (uint32_t)(((1ull << 32) + d - 1) / d);
+}
+__device__ __forceinline__ uint32_t fast_div(uint32_t x, uint32_t magic) {
+  return magic ? __umulhi(x, magic) : x;
+}
+
+struct AnyArgs {
+  int T, n1, n2, n3, d1, d2, d3, R, D, sched;
+  int ident;   // two cores: the middle core is the identity, C is A
+  int sq;      // slices per stack
+  int rows12;  // d1 d2
+  int d2R;
+  int pitch;   // LDS floats per C row: an odd multiple of 4, so that 16 rows start on 16 distinct bank groups
+  int tile;    // LDS floats per wave
+  uint32_t mR, md1, md3;  // div_magic of R, d1, d3
+};
+
+// Slices of a stack: their d1 rows of A fill one 16-row tile
+int any_stack_slices(const Shape& s) { return s.d1 >= 16 ? 1 : 16 / s.d1; }
+
+static AnyArgs any_args(const Shape& s) {
+  AnyArgs a;
+  a.T = s.T;
+  a.n1 = s.n1;
+  a.n2 = s.n2;
+  a.n3 = s.n3;
+  a.d1 = s.d1;
+  a.d2 = s.d2;
+  a.d3 = s.d3;
+  a.R = s.R;
+  a.D = s.D;
+  a.sched = s.sched;
+  a.ident = s.L == 2;
+  a.sq = any_stack_slices(s);
+  a.rows12 = s.d1 * s.d2;
+  a.d2R = s.d2 * s.R;
+  a.pitch = 4 * (((s.R + 3) / 4) | 1);
+  a.tile = a.sq * a.rows12 * a.pitch;
+  a.mR = div_magic(s.R);
+  a.md1 = div_magic(s.d1);
+  a.md3 = div_magic(s.d3);
+  return a;
+}
+
+// Floats k .. k + 3 of the vector p[0 .. n - 1], zeros past its end; FULL: all four are
+// there and p is 16-byte aligned.  The loads past the end read the last element instead:
+// a load under a condition would be a branch of its own with its own wait.
+template <bool FULL>
+__device__ __forceinline__ f32x4 load4(const float* p, int k, int n) {
+  if (FULL) return *reinterpret_cast<const f32x4*>(p + k);
+  f32x4 v;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) v[i] = p[k + i < n ? k + i : n - 1];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) v[i] = k + i < n ? v[i] : 0.f;
+  return v;
+}
+
+// The stack a wave works on: lane j < nq holds slice j (other lanes no rows), and the
+// tiles of its slices are numbered through: lane j's end at tile_end.
+struct Stack {
+  int nq;        // slices (wave-uniform)
+  int rb, nr, i1;  // per lane: first row, rows, first digit
+  int tile_end;  // per lane: tiles of slices 0 .. lane
+  int ntiles;    // of the whole stack (wave-uniform)
+};
+__device__ __forceinline__ void load_stack(Stack& k, const AnyArgs& s, const int4* __restrict__ slices,
+                                           const int32_t* __restrict__ slice_i1, int f, int nq) {
+  const int lane = lane_id();
+  k.nq = nq;
+  k.rb = k.nr = k.i1 = 0;
+  if (lane < nq) {
+    const int4 sd = slices[f + lane];
+    k.rb = sd.y;
+    k.nr = sd.z - sd.y;
+    k.i1 = slice_i1[f + lane];
+  }
+  k.tile_end = wave_incl_scan<int>((k.nr * s.d3 + 15) >> 4);
+  k.ntiles = __builtin_amdgcn_readlane(k.tile_end, 63);
+}
+// Slice and first item of tile P (P < ntiles)
+struct TileAt {
+  int j, rb, nitems, item0;  // wave-uniform; item0: the tile's first item within the slice
+};
+__device__ __forceinline__ TileAt tile_at(const Stack& k, const AnyArgs& s, int P) {
+  TileAt a;
+  a.j = __builtin_ctzll(__ballot(k.tile_end > P));
+  a.rb = __builtin_amdgcn_readlane(k.rb, a.j);
+  a.nitems = __builtin_amdgcn_readlane(k.nr, a.j) * s.d3;
+  const int before = a.j > 0 ? __builtin_amdgcn_readlane(k.tile_end, a.j - 1) : 0;
+  a.item0 = 16 * (P - before);
+  return a;
+}
+
+// Stage 1: C of the stack into the wave's LDS tile.  FULL: R = 16 KC.
+template <int KC, bool FULL>
+__device__ __forceinline__ void stage1(const AnyArgs& s, const Stack& k, const float* __restrict__ G1,
+                                       const float* __restrict__ B, int t, float* scr) {
+  const int lane = lane_id(), l15 = lane & 15, l4 = lane >> 4;
+  const int rows = k.nq * s.d1;  // rows of A in the stack
+  for (int m0 = 0; m0 < rows; m0 += 16) {
+    // A operand: row m = (slice, j1) in lane l15, a = 16 c + 4 l4 + i (rows past the
+    // stack's repeat the last; their products are not stored)
+    const int m = m0 + l15 < rows ? m0 + l15 : rows - 1;
+    const int j = (int)fast_div((uint32_t)m, s.md1);
+    const int i1 = __shfl(k.i1, j, 64);
+    const float* A = G1 + ((int64_t)(t * (int64_t)s.n1 + i1) * s.d1 + (m - j * s.d1)) * s.R;
+    f32x4 Aop[KC];
+#pragma unroll
+    for (int c = 0; c < KC; ++c) Aop[c] = load4<FULL>(A, 16 * c + 4 * l4, s.R);
+    if (s.ident) {
+      if (m0 + l15 < rows)
+#pragma unroll
+        for (int c = 0; c < KC; ++c)
+          if (FULL || 16 * c + 4 * l4 < s.pitch)
+            *reinterpret_cast<f32x4*>(scr + (m0 + l15) * s.pitch + 16 * c + 4 * l4) = Aop[c];
+      continue;
+    }
+    for (int n0 = 0; n0 < s.d2R; n0 += 16) {
+      const int col = n0 + l15;
+      const float* Bc = B + (col < s.d2R ? col : s.d2R - 1);
+      float bv[KC][4];
+#pragma unroll
+      for (int c = 0; c < KC; ++c)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int a = 16 * c + 4 * l4 + i;
+          bv[c][i] = Bc[(FULL || a < s.R ? a : s.R - 1) * s.d2R];
+        }
+      if (!FULL)
+#pragma unroll
+        for (int c = 0; c < KC; ++c)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) bv[c][i] = 16 * c + 4 * l4 + i < s.R ? bv[c][i] : 0.f;
+      f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int c = 0; c < KC; ++c)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(Aop[c][i], bv[c][i], acc, 0, 0, 0);
+      // lane holds rows m0 + 4 l4 + r of column col = (j2, b)
+      const int j2 = (int)fast_div((uint32_t)col, s.mR);
+      const int b = col - j2 * s.R;
+      if (col < s.d2R)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          if (m0 + 4 * l4 + r < rows) scr[((m0 + 4 * l4 + r) * s.d2 + j2) * s.pitch + b] = acc[r];
+    }
+  }
+}
+
+// The next chunk of a one-wave worker: its fixed share (static modes) or a claim
+struct Claim {
+  Worker worker;
+  int next, hi;
+};
+__device__ __forceinline__ int claim_wave(Claim& k, int sched, int32_t* q, int nch) {
+  if (sched_static(sched)) return k.next < k.hi ? k.next++ : -1;
+  return claim_queues(q, nch, &k.worker);
+}
+
+// ---------------------------------------------------------------------------
+// forward
+// ---------------------------------------------------------------------------
+// D3 = d3 (2, 4 or 8) with R = 16 KC and d1 d2 <= 16, or 0: any shape
+template <int KC, int D3>
+__global__ void __launch_bounds__(256, KC == 1 ? 6 : (KC == 2 ? 5 : 3)) k_fwd_any(AnyArgs s, const float* __restrict__ G1,
+                                                 const float* __restrict__ G2, const float* __restrict__ G3,
+                                                 const int4* __restrict__ slices,
+                                                 const int32_t* __restrict__ slice_i1,
+                                                 const int4* __restrict__ chunks,
+                                                 const uint32_t* __restrict__ run_base,
+                                                 const int32_t* __restrict__ uniq_i3, int32_t* __restrict__ ctr,
+                                                 float* __restrict__ E) {
+  constexpr bool FULL = D3 != 0;
+  const int d3 = FULL ? D3 : s.d3;
+  extern __shared__ f32x4 lds4[];
+  const int lane = lane_id(), l15 = lane & 15, l4 = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nw = blockDim.x >> 6;
+  float* scr = reinterpret_cast<float*>(lds4) + wave * s.tile;
+  const int nch = (int)run_base[s.T * s.n2];
+  const int wid = blockIdx.x * nw + wave, nwt = gridDim.x * nw;
+  __shared__ int left_behind;
+  if (threadIdx.x == 0) left_behind = 0;
+  __syncthreads();
+  Claim cl = {make_worker(SCHED_NQ, nw, wave, &left_behind), share_lo(nch, nwt, wid), share_lo(nch, nwt, wid + 1)};
+
+  struct Tile {
+    f32x4 d[KC];  // D^T[item l15][b = 16 c + 4 l4 + i]
+    TileAt at;
+  };
+  Stack k;
+  int t = 0;
+  // i3 of this lane's item of tile P, one tile ahead of the G3 loads that need it
+  auto load_i3 = [&](int P) {
+    const TileAt a = tile_at(k, s, P);
+    const int item = a.item0 + l15 < a.nitems ? a.item0 + l15 : a.nitems - 1;
+    return uniq_i3[a.rb + (FULL ? item / D3 : (int)fast_div((uint32_t)item, s.md3))];
+  };
+  auto load_tile = [&](Tile& X, int P, int i3) {
+    X.at = tile_at(k, s, P);
+    const int item = X.at.item0 + l15 < X.at.nitems ? X.at.item0 + l15 : X.at.nitems - 1;
+    const int j3 = FULL ? item % D3 : item - (int)fast_div((uint32_t)item, s.md3) * d3;
+    const float* g = G3 + ((int64_t)t * s.n3 + i3) * (s.R * d3) + j3;
+#pragma unroll
+    for (int c = 0; c < KC; ++c)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int b = 16 * c + 4 * l4 + i;
+        X.d[c][i] = g[(FULL || b < s.R ? b : s.R - 1) * d3];  // ranks past R are zeroed below
+      }
+  };
+  auto compute = [&](Tile& X) {
+    if (!FULL)
+#pragma unroll
+      for (int c = 0; c < KC; ++c)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) X.d[c][i] = 16 * c + 4 * l4 + i < s.R ? X.d[c][i] : 0.f;
+    const float* Cj = scr + X.at.j * s.rows12 * s.pitch;
+    for (int jt = 0; jt < (FULL ? 16 : s.rows12); jt += 16) {
+      const int jj = jt + l15;
+      const float* cr = Cj + (jj < s.rows12 ? jj : s.rows12 - 1) * s.pitch;
+      f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int c = 0; c < KC; ++c) {
+        const f32x4 ct = load4<FULL>(cr, 16 * c + 4 * l4, s.R);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(X.d[c][i], ct[i], acc, 0, 0, 0);
+      }
+      // lane holds items item0 + 4 l4 + r of column jj
+      const int it = X.at.item0 + 4 * l4;
+      if (jj < s.rows12) {
+        float* Eb = E + (int64_t)X.at.rb * s.D + jj * d3;
+        if (D3 == 8 || D3 == 4) {
+          if (it < X.at.nitems) *reinterpret_cast<f32x4*>(Eb + (it / (FULL ? D3 : 1)) * s.D + it % (FULL ? D3 : 1)) = acc;
+        } else if (D3 == 2) {
+          typedef float f32x2 __attribute__((ext_vector_type(2)));
+          if (it < X.at.nitems) *reinterpret_cast<f32x2*>(Eb + (it / 2) * s.D) = f32x2{acc[0], acc[1]};
+          if (it + 2 < X.at.nitems) *reinterpret_cast<f32x2*>(Eb + (it / 2 + 1) * s.D) = f32x2{acc[2], acc[3]};
+        } else {
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            if (it + r < X.at.nitems) {
+              const int row = (int)fast_div((uint32_t)(it + r), s.md3);
+              Eb[(int64_t)row * s.D + (it + r - row * d3)] = acc[r];
+            }
+        }
+      }
+    }
+  };
+  int c;
+  while ((c = claim_wave(cl, s.sched, ctr + C_FWD_CTR, nch)) >= 0) {
+    const int4 ch = chunks[c];
+    const int f = __builtin_amdgcn_readfirstlane(ch.x), ns = __builtin_amdgcn_readfirstlane(ch.y);
+    const int run = __builtin_amdgcn_readfirstlane(ch.z);
+    t = run / s.n2;
+    const float* B = G2 + (int64_t)run * s.R * s.d2R;
+    for (int q = 0; q < ns; q += s.sq) {
+      load_stack(k, s, slices, slice_i1, f + q, ns - q < s.sq ? ns - q : s.sq);
+      Tile X, Y;
+      // the first tile's operands load while stage 1 runs
+      const int last = k.ntiles - 1;
+      int i3a = load_i3(0), i3b = load_i3(last < 1 ? last : 1);
+      load_tile(X, 0, i3a);
+      stage1<KC, FULL>(s, k, G1, B, t, scr);
+      wave_lds_sync();
+      for (int P = 0; P <= last; P += 2) {
+        i3a = load_i3(P + 2 < last ? P + 2 : last);
+        load_tile(Y, P + 1 < last ? P + 1 : last, i3b);
+        compute(X);
+        if (P + 1 > last) break;
+        i3b = load_i3(P + 3 < last ? P + 3 : last);
+        load_tile(X, P + 2 < last ? P + 2 : last, i3a);
+        compute(Y);
+      }
+      wave_lds_sync();  // the tile is rewritten by the next stack
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------
+// backward
+// ---------------------------------------------------------------------------
+// Instances as for the forward.  Writes dD of every row, and per slice dC (not with the
+// identity middle core) and dA; every partial is written by one wave, so the segment sums
+// over them are reproducible bit for bit.
+template <int KC, int D3>
+__global__ void __launch_bounds__(256, KC == 1 ? 4 : (KC == 2 ? 3 : 2)) k_bwd_any(AnyArgs s, const float* __restrict__ G1,
+                                                 const float* __restrict__ G2, const float* __restrict__ G3,
+                                                 const float* __restrict__ dE, const int4* __restrict__ slices,
+                                                 const int32_t* __restrict__ slice_i1,
+                                                 const int4* __restrict__ chunks,
+                                                 const uint32_t* __restrict__ run_base,
+                                                 const int32_t* __restrict__ uniq_i3, int32_t* __restrict__ ctr,
+                                                 float* __restrict__ dApart, float* __restrict__ dCpart,
+                                                 float* __restrict__ dDpart) {
+  constexpr bool FULL = D3 != 0;
+  constexpr int D3V = FULL ? D3 : 1;
+  const int d3 = FULL ? D3 : s.d3;
+  const int RD = s.R * d3;
+  extern __shared__ f32x4 lds4[];
+  const int lane = lane_id(), l15 = lane & 15, l4 = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nw = blockDim.x >> 6;
+  float* scr = reinterpret_cast<float*>(lds4) + wave * s.tile;
+  const int nch = (int)run_base[s.T * s.n2];
+  const int wid = blockIdx.x * nw + wave, nwt = gridDim.x * nw;
+  __shared__ int left_behind;
+  if (threadIdx.x == 0) left_behind = 0;
+  __syncthreads();
+  Claim cl = {make_worker(SCHED_NQ, nw, wave, &left_behind), share_lo(nch, nwt, wid), share_lo(nch, nwt, wid + 1)};
+
+  struct Tile {
+    float e1[4];  // dE[jj = jt + 4 i + l4] of item l15: the dD product's A operand
+    f32x4 e2;     // dE[jj = jt + l15] of items 4 l4 + i: the dC product's A operand
+    f32x4 g[KC];  // G3[i3][b = 16 c + l15] of items 4 l4 + i: the dC product's B operand
+    TileAt at;
+  };
+  Stack k;
+  int t = 0;
+  auto clamp_item = [&](const TileAt& a, int x) { return a.item0 + x < a.nitems ? a.item0 + x : a.nitems - 1; };
+  auto row_of = [&](int item) { return FULL ? item / D3V : (int)fast_div((uint32_t)item, s.md3); };
+  auto load_i3 = [&](int P) {
+    const TileAt a = tile_at(k, s, P);
+    return uniq_i3[a.rb + row_of(clamp_item(a, l15))];
+  };
+  auto load_e1 = [&](Tile& X, int jt) {
+    const int item = clamp_item(X.at, l15), row = row_of(item);
+    const float* e = dE + (int64_t)(X.at.rb + row) * s.D + (item - row * d3);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int jj = jt + 4 * i + l4;
+      X.e1[i] = e[(jj < s.rows12 ? jj : s.rows12 - 1) * d3];
+    }
+  };
+  // i3: that of item l15, from load_i3; rows and columns past the end repeat the last one
+  // here and are zeroed before the products
+  auto load_e2g = [&](Tile& X, int i3, int jt) {
+    const int jj = jt + l15 < s.rows12 ? jt + l15 : s.rows12 - 1;
+    const float* Et = dE + (int64_t)X.at.rb * s.D + jj * d3;
+    const float* Gt = G3 + (int64_t)t * s.n3 * RD;
+    if (D3 == 4 || D3 == 8) {
+      int it = X.at.item0 + 4 * l4;
+      it = it < X.at.nitems ? it : X.at.nitems - 4;
+      const int i = __shfl(i3, it - X.at.item0, 64);
+      X.e2 = *reinterpret_cast<const f32x4*>(Et + (it / D3V) * s.D + it % D3V);
+#pragma unroll
+      for (int c = 0; c < KC; ++c)
+        X.g[c] = *reinterpret_cast<const f32x4*>(Gt + (int64_t)i * RD + (16 * c + l15) * D3V + it % D3V);
+    } else if (D3 == 2) {
+      typedef float f32x2 __attribute__((ext_vector_type(2)));
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        int it = X.at.item0 + 4 * l4 + 2 * h;
+        it = it < X.at.nitems ? it : X.at.nitems - 2;
+        const int i = __shfl(i3, it - X.at.item0, 64);
+        const f32x2 e = *reinterpret_cast<const f32x2*>(Et + (it / 2) * s.D);
+        X.e2[2 * h] = e[0];
+        X.e2[2 * h + 1] = e[1];
+#pragma unroll
+        for (int c = 0; c < KC; ++c) {
+          const f32x2 v = *reinterpret_cast<const f32x2*>(Gt + (int64_t)i * RD + (16 * c + l15) * 2);
+          X.g[c][2 * h] = v[0];
+          X.g[c][2 * h + 1] = v[1];
+        }
+      }
+    } else {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int it = clamp_item(X.at, 4 * l4 + q);
+        const int row = row_of(it), j3 = it - row * d3;
+        const int i = __shfl(i3, it - X.at.item0, 64);
+        X.e2[q] = Et[(int64_t)row * s.D + j3];
+#pragma unroll
+        for (int c = 0; c < KC; ++c) {
+          const int b = 16 * c + l15 < s.R ? 16 * c + l15 : s.R - 1;
+          X.g[c][q] = Gt[(int64_t)i * RD + b * d3 + j3];
+        }
+      }
+    }
+  };
+  // C of slice j as the dD product's B operand: C[jj = jt + 4 i + l4][b = 16 c + l15]
+  float CB[KC][4];
+  auto load_CB = [&](int j, int jt) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int jj = jt + 4 * i + l4;
+      const float* cr = scr + (j * s.rows12 + (jj < s.rows12 ? jj : s.rows12 - 1)) * s.pitch;
+#pragma unroll
+      for (int c = 0; c < KC; ++c) {
+        const float v = cr[FULL || 16 * c + l15 < s.pitch ? 16 * c + l15 : 0];
+        CB[c][i] = jj < s.rows12 ? v : 0.f;
+      }
+    }
+  };
+  f32x4 dD[KC], dC[KC];
+  auto add_dD = [&](const Tile& X, int jt) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      if (jt + 4 * i >= s.rows12) break;
+      const float e = jt + 4 * i + l4 < s.rows12 ? X.e1[i] : 0.f;
+#pragma unroll
+      for (int c = 0; c < KC; ++c) dD[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(e, CB[c][i], dD[c], 0, 0, 0);
+    }
+  };
+  // lane holds dD[item item0 + 4 l4 + r][b = 16 c + l15]
+  auto store_dD = [&](const Tile& X) {
+    const int it = X.at.item0 + 4 * l4;
+    float* base = dDpart + (int64_t)X.at.rb * RD;
+#pragma unroll
+    for (int c = 0; c < KC; ++c) {
+      const int b = 16 * c + l15;
+      if (!FULL && b >= s.R) continue;
+      if (D3 == 4 || D3 == 8) {
+        if (it < X.at.nitems)
+          *reinterpret_cast<f32x4*>(base + (it / D3V) * RD + b * D3V + it % D3V) = dD[c];
+      } else if (D3 == 2) {
+        typedef float f32x2 __attribute__((ext_vector_type(2)));
+        if (it < X.at.nitems) *reinterpret_cast<f32x2*>(base + (it / 2) * RD + 2 * b) = f32x2{dD[c][0], dD[c][1]};
+        if (it + 2 < X.at.nitems)
+          *reinterpret_cast<f32x2*>(base + (it / 2 + 1) * RD + 2 * b) = f32x2{dD[c][2], dD[c][3]};
+      } else {
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          if (it + r < X.at.nitems) {
+            const int row = row_of(it + r);
+            base[(int64_t)row * RD + b * d3 + (it + r - row * d3)] = dD[c][r];
+          }
+      }
+    }
+  };
+  auto add_dC = [&](const Tile& X) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const bool ok = X.at.item0 + 4 * l4 + i < X.at.nitems;
+      const float e = ok ? X.e2[i] : 0.f;
+#pragma unroll
+      for (int c = 0; c < KC; ++c)
+        dC[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(e, ok ? X.g[c][i] : 0.f, dC[c], 0, 0, 0);
+    }
+  };
+  auto zero = [&](f32x4(&v)[KC]) {
+#pragma unroll
+    for (int c = 0; c < KC; ++c) v[c] = f32x4{0.f, 0.f, 0.f, 0.f};
+  };
+  // lane holds dC[jj = jt + 4 l4 + r][b = 16 c + l15] of slice j: in place of C_j, and the
+  // slice's partial; with the identity middle core it is dA
+  auto store_dC = [&](int first, int j, int jt) {
+    wave_lds_sync();
+    float* out = (s.ident ? dApart : dCpart) + (int64_t)(first + j) * s.rows12 * s.R;
+#pragma unroll
+    for (int c = 0; c < KC; ++c) {
+      const int b = 16 * c + l15;
+      if (!FULL && b >= s.R) continue;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int jj = jt + 4 * l4 + r;
+        if (jj < s.rows12) {
+          scr[(j * s.rows12 + jj) * s.pitch + b] = dC[c][r];
+          __builtin_nontemporal_store(dC[c][r], out + jj * s.R + b);
+        }
+      }
+    }
+  };
+  int c;
+  while ((c = claim_wave(cl, s.sched, ctr + C_BWD_CTR, nch)) >= 0) {
+    const int4 ch = chunks[c];
+    const int f = __builtin_amdgcn_readfirstlane(ch.x), ns = __builtin_amdgcn_readfirstlane(ch.y);
+    const int run = __builtin_amdgcn_readfirstlane(ch.z);
+    t = run / s.n2;
+    const float* B = G2 + (int64_t)run * s.R * s.d2R;
+    for (int q = 0; q < ns; q += s.sq) {
+      load_stack(k, s, slices, slice_i1, f + q, ns - q < s.sq ? ns - q : s.sq);
+      const int last = k.ntiles - 1;
+      if (FULL || s.rows12 <= 16) {
+        Tile X, Y;
+        auto load_tile = [&](Tile& Z, int P, int i3) {
+          Z.at = tile_at(k, s, P);
+          load_e1(Z, 0);
+          load_e2g(Z, i3, 0);
+        };
+        int i3a = load_i3(0), i3b = load_i3(last < 1 ? last : 1);
+        load_tile(X, 0, i3a);  // loads while stage 1 runs
+        stage1<KC, FULL>(s, k, G1, B, t, scr);
+        wave_lds_sync();
+        int cj = 0;
+        load_CB(0, 0);
+        zero(dC);
+        auto step = [&](const Tile& Z) {
+          if (Z.at.j != cj) {
+            store_dC(f + q, cj, 0);
+            cj = Z.at.j;
+            load_CB(cj, 0);
+            zero(dC);
+          }
+          zero(dD);
+          add_dD(Z, 0);
+          add_dC(Z);
+          store_dD(Z);
+        };
+        for (int P = 0; P <= last; P += 2) {
+          i3a = load_i3(P + 2 < last ? P + 2 : last);
+          load_tile(Y, P + 1 < last ? P + 1 : last, i3b);
+          step(X);
+          if (P + 1 > last) break;
+          i3b = load_i3(P + 3 < last ? P + 3 : last);
+          load_tile(X, P + 2 < last ? P + 2 : last, i3a);
+          step(Y);
+        }
+        store_dC(f + q, cj, 0);
+      } else {
+        // C of a slice spans several 16-row tiles: every dD of the slice first, then its
+        // dC one 16-row tile at a time
+        stage1<KC, FULL>(s, k, G1, B, t, scr);
+        wave_lds_sync();
+        for (int P0 = 0; P0 <= last;) {
+          const int j = tile_at(k, s, P0).j, P1 = __builtin_amdgcn_readlane(k.tile_end, j);
+          Tile X;
+          for (int P = P0; P < P1; ++P) {
+            X.at = tile_at(k, s, P);
+            zero(dD);
+            for (int jt = 0; jt < s.rows12; jt += 16) {
+              load_e1(X, jt);
+              load_CB(j, jt);
+              add_dD(X, jt);
+            }
+            store_dD(X);
+          }
+          for (int jt = 0; jt < s.rows12; jt += 16) {
+            zero(dC);
+            for (int P = P0; P < P1; ++P) {
+              X.at = tile_at(k, s, P);
+              load_e2g(X, load_i3(P), jt);
+              add_dC(X);
+            }
+            store_dC(f + q, j, jt);
+          }
+          P0 = P1;
+        }
+      }
+      wave_lds_sync();
+      if (!s.ident) {
+        // dA (stack rows x R) = dC (stack rows x d2 R) . B^T, contraction (j2, b = 16 c + 4 l4 + i)
+        const int rows = k.nq * s.d1;
+        for (int m0 = 0; m0 < rows; m0 += 16) {
+          const int m = m0 + l15 < rows ? m0 + l15 : rows - 1;
+          f32x4 acc[KC];
+          zero(acc);
+#pragma unroll 2
+          for (int j2 = 0; j2 < s.d2; ++j2) {
+#pragma unroll
+            for (int cc = 0; cc < KC; ++cc) {
+              const int b = 16 * cc + 4 * l4;
+              const f32x4 av = load4<FULL>(scr + (m * s.d2 + j2) * s.pitch, b, s.R);
+#pragma unroll
+              for (int at = 0; at < KC; ++at) {
+                const int a = FULL || 16 * at + l15 < s.R ? 16 * at + l15 : s.R - 1;
+                const f32x4 bv = load4<FULL>(B + a * s.d2R + j2 * s.R, b, s.R);
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                  acc[at] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[i], bv[i], acc[at], 0, 0, 0);
+              }
+            }
+          }
+          // lane holds dA[stack row m0 + 4 l4 + r][a = 16 at + l15]
+          float* out = dApart + (int64_t)(f + q) * s.d1 * s.R;
+#pragma unroll
+          for (int at = 0; at < KC; ++at)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+              if (m0 + 4 * l4 + r < rows && (FULL || 16 * at + l15 < s.R))
+                __builtin_nontemporal_store(acc[at][r], out + (m0 + 4 * l4 + r) * s.R + 16 * at + l15);
+        }
+        wave_lds_sync();  // the tile is rewritten by the next stack
+      }
+    }
+  }
+}
+
+// dG2[t][i2] (R x d2 R) = sum over the slices of run (t, i2), in slice order, of A^T . dC,
+// A = G1[t][i1 of the slice] (d1 x R) and dC the slice's partial (d1 x d2 R): a product
+// contracted over (slice, j1).  Block (run, y): its sixteen waves take cw tiles of 16 of
+// the d2 R columns times 16 / cw parts of the contraction, each with all rows a in KC
+// accumulators, and the parts are added in order through LDS (the same bits run to run).
+// Splitting the contraction is what fills the waves at small d2 R, where a run has one to
+// four column tiles but hundreds of slices.  With `update`, dG2 is G2 and receives
+// G2 - lr sum; G1 must not have been updated yet.
+constexpr int DGA_WAVES = 16;
+constexpr int DGA_STEPS = 4;  // contraction steps whose loads are in flight together
+template <int KC>
+__global__ void __launch_bounds__(64 * DGA_WAVES) k_dg2_any(AnyArgs s, int cw, const float* __restrict__ G1,
+                                                            const uint32_t* __restrict__ dense_base,
+                                                            const int32_t* __restrict__ slice_i1,
+                                                            const int32_t* __restrict__ ctr,
+                                                            const float* __restrict__ dCpart,
+                                                            float* __restrict__ dG2, float lr, bool update) {
+  __shared__ float red[DGA_WAVES][4 * KC][64];
+  const int run = blockIdx.x, t = run / s.n2;
+  const int lane = lane_id(), w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int l15 = lane & 15, l4 = lane >> 4;
+  const int parts = DGA_WAVES / cw, ct = w % cw, part = w / cw;
+  const int64_t slot0 = (int64_t)run * s.n1;
+  const int lo = (int)dense_base[slot0];
+  const int hi = run + 1 < s.T * s.n2 ? (int)dense_base[slot0 + s.n1] : ctr[C_NSLICES];
+  const int64_t nk = (int64_t)(hi - lo) * s.d1;  // contraction rows (slice, j1)
+  const int64_t nsteps = (nk + 3) / 4;
+  const int64_t k0 = nsteps * part / parts, k1 = nsteps * (part + 1) / parts;
+  const int col = 16 * (blockIdx.y * cw + ct) + l15;
+  const int colc = col < s.d2R ? col : s.d2R - 1;
+  f32x4 acc[KC];
+#pragma unroll
+  for (int c = 0; c < KC; ++c) acc[c] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const float* G1t = G1 + (int64_t)t * s.n1 * s.d1 * s.R;
+  const float* dCr = dCpart + (int64_t)lo * s.d1 * s.d2R + colc;
+  // this lane's contraction row 4 step + l4 as (slice, j1), kept by increments
+  int64_t sl = (4 * k0 + l4) / s.d1;
+  int j1 = (int)(4 * k0 + l4 - sl * s.d1);
+  for (int64_t step = k0; step < k1; step += DGA_STEPS) {
+    float a[DGA_STEPS][KC], b[DGA_STEPS];
+    bool ok[DGA_STEPS];
+#pragma unroll
+    for (int u = 0; u < DGA_STEPS; ++u) {
+      const int64_t kk = 4 * (step + u) + l4;
+      ok[u] = step + u < k1 && kk < nk;
+      const int i1 = slice_i1[lo + (ok[u] ? sl : 0)];
+      const float* Ar = G1t + ((int64_t)i1 * s.d1 + j1) * s.R;
+#pragma unroll
+      for (int c = 0; c < KC; ++c) a[u][c] = Ar[16 * c + l15 < s.R ? 16 * c + l15 : s.R - 1];
+      b[u] = ntl(dCr + (ok[u] ? kk : 0) * s.d2R);
+      j1 += 4;
+      while (j1 >= s.d1) {
+        j1 -= s.d1;
+        ++sl;
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < DGA_STEPS; ++u)
+#pragma unroll
+      for (int c = 0; c < KC; ++c)
+        acc[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(ok[u] ? a[u][c] : 0.f, ok[u] ? b[u] : 0.f, acc[c], 0, 0, 0);
+  }
+  if (part > 0) {
+#pragma unroll
+    for (int c = 0; c < KC; ++c)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) red[w][4 * c + r][lane] = acc[c][r];
+  }
+  __syncthreads();
+  if (part == 0 && col < s.d2R) {
+    // lane holds dG2[a = 16 c + 4 l4 + r][col]
+    float* out = dG2 + (int64_t)run * s.R * s.d2R + col;
+#pragma unroll
+    for (int c = 0; c < KC; ++c)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int a = 16 * c + 4 * l4 + r;
+        if (a >= s.R) continue;
+        float v = acc[c][r];
+        for (int p = 1; p < parts; ++p) v += red[w + p * cw][4 * c + r][lane];
+        float* o = out + a * s.d2R;
+        *o = update ? *o - lr * v : v;
+      }
+  }
+}
+
+// ---------------------------------------------------------------------------
+// launch
+// ---------------------------------------------------------------------------
+constexpr size_t ANY_LDS = 160 * 1024 - 1024;
+
+// Waves per block and blocks per CU: four-wave blocks while their LDS tiles leave room for
+// at least two blocks per CU, else one-wave blocks; at most eight waves per SIMD.
+static void any_grid(const AnyArgs& a, int* waves, int* blocks, size_t* lds) {
+  const size_t tile = sizeof(float) * (size_t)a.tile;
+  *waves = 8 * tile <= ANY_LDS ? 4 : 1;
+  *lds = tile * *waves;
+  int per_cu = (int)(ANY_LDS / *lds);
+  if (per_cu > 32 / *waves) per_cu = 32 / *waves;
+  if (per_cu < 1) per_cu = 1;
+  *blocks = persistent_grid() * per_cu;
+}
+
+// d3 with its own instance at rank 16, 32 or 64 and up to 16 rows of C, else 0
+static int any_d3(const Shape& s) {
+  const bool full = (s.R == 16 || s.R == 32 || s.R == 64) && s.d1 * s.d2 <= 16;
+  return full && (s.d3 == 2 || s.d3 == 4 || s.d3 == 8) ? s.d3 : 0;
+}
+
+template <int KC>
+static const void* fwd_any_kernel(int d3) {
+  switch (d3) {
+    case 2: return (const void*)k_fwd_any<KC, 2>;
+    case 4: return (const void*)k_fwd_any<KC, 4>;
+    case 8: return (const void*)k_fwd_any<KC, 8>;
+    default: return (const void*)k_fwd_any<KC, 0>;
+  }
+}
+
+hipError_t launch_fwd_any(const Shape& s, const Work& w, const float* G1, const float* G2, const float* G3,
+                          const Prof& prof, hipStream_t st) {
+  AnyArgs a = any_args(s);
+  int waves, blocks;
+  size_t lds;
+  any_grid(a, &waves, &blocks, &lds);
+  const int d3 = any_d3(s);
+  const void* fn = s.R <= 16 ? fwd_any_kernel<1>(d3) : (s.R <= 32 ? fwd_any_kernel<2>(d3) : fwd_any_kernel<4>(d3));
+  hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  if (e != hipSuccess) return e;
+  const int4 *slices = w.slices, *chunks = w.chunks;
+  const int32_t *i1 = w.slice_i1, *i3 = w.uniq_i3;
+  const uint32_t* rb = w.run_nch;
+  int32_t* ctr = w.ctr;
+  float* E = w.E;
+  void* args[] = {&a, &G1, &G2, &G3, &slices, &i1, &chunks, &rb, &i3, &ctr, &E};
+  prof_begin(prof, K_FWD_FUSED, st);
+  e = hipLaunchKernel(fn, dim3(blocks), dim3(64 * waves), args, lds, st);
+  prof_end(prof, K_FWD_FUSED, st);
+  return e != hipSuccess ? e : hipGetLastError();
+}
+
+template <int KC>
+static const void* bwd_any_kernel(int d3) {
+  switch (d3) {
+    case 2: return (const void*)k_bwd_any<KC, 2>;
+    case 4: return (const void*)k_bwd_any<KC, 4>;
+    case 8: return (const void*)k_bwd_any<KC, 8>;
+    default: return (const void*)k_bwd_any<KC, 0>;
+  }
+}
+
+// The claim counters must be zero.
+hipError_t launch_bwd_any(const Shape& s, const Work& w, const float* G1, const float* G2, const float* G3,
+                          const Prof& prof, hipStream_t st) {
+  AnyArgs a = any_args(s);
+  if (!w.dDpart || (!a.ident && !w.dCpart)) return hipErrorInvalidValue;
+  int waves, blocks;
+  size_t lds;
+  any_grid(a, &waves, &blocks, &lds);
+  const int d3 = any_d3(s);
+  const void* fn = s.R <= 16 ? bwd_any_kernel<1>(d3) : (s.R <= 32 ? bwd_any_kernel<2>(d3) : bwd_any_kernel<4>(d3));
+  hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  if (e != hipSuccess) return e;
+  const int4 *slices = w.slices, *chunks = w.chunks;
+  const int32_t *i1 = w.slice_i1, *i3 = w.uniq_i3;
+  const uint32_t* rb = w.run_nch;
+  int32_t* ctr = w.ctr;
+  const float* dE = w.E;
+  float *dA = w.dApart, *dC = w.dCpart, *dD = w.dDpart;
+  void* args[] = {&a, &G1, &G2, &G3, &dE, &slices, &i1, &chunks, &rb, &i3, &ctr, &dA, &dC, &dD};
+  prof_begin(prof, K_BWD_FUSED, st);
+  e = hipLaunchKernel(fn, dim3(blocks), dim3(64 * waves), args, lds, st);
+  prof_end(prof, K_BWD_FUSED, st);
+  return e != hipSuccess ? e : hipGetLastError();
+}
+
+hipError_t launch_dg2_any(const Shape& s, const Work& w, const float* G1, float* dG2, float lr, bool update,
+                          hipStream_t st) {
+  const AnyArgs a = any_args(s);
+  const int nt = (a.d2R + 15) / 16;
+  int cw = 1;
+  while (cw < nt && cw < DGA_WAVES) cw *= 2;
+  const dim3 grid(s.T * s.n2, (nt + cw - 1) / cw);
+  auto fn = s.R <= 16 ? k_dg2_any<1> : (s.R <= 32 ? k_dg2_any<2> : k_dg2_any<4>);
+  hipLaunchKernelGGL(fn, grid, dim3(64 * DGA_WAVES), 0, st, a, cw, G1, (const uint32_t*)w.dense_base,
+                     (const int32_t*)w.slice_i1, (const int32_t*)w.ctr, (const float*)w.dCpart, dG2, lr, update);
+  return hipGetLastError();
+}
+
+}  // namespace ttemb

@@ -394,17 +394,15 @@ __global__ void __launch_bounds__(64 * FIX_WAVES) k_seg_fix(const int32_t* __res
 }
 
 // ---------------------------------------------------------------------------
-// generic backward (any shape; plain VALU).  A block claims a chunk: up to 32
-// consecutive slices of one (t, i2) run, so every slice of it has the same
-// B = G2[t][i2], which is staged in LDS once per chunk (rows padded by one float,
-// so reads across a's take distinct banks) when it fits.  Per slice: A staged; C
-// recomputed (or reloaded from the checkpoint); the slice's rows in batches whose
-// dE rows are staged together: dD per row into dG3, the rows' dC summed; then dA
-// into the slice's partial and dB = A^T (sum dC) summed over the chunk (in LDS
-// when it fits, else in the chunk's partial in global memory, each element owned
-// by one thread) into the chunk's partial; dD of every row into the row's partial.
-// No two blocks write one partial, and the fixed-order segment sums below turn the
-// partials into dG1 (over the slices of (t, i1)), dG2 (over the chunks of
+// Backward with checkpointed intermediates (SCHED_STEAL_CKPT on a shape without a
+// specialised kernel; plain VALU).  A block claims a chunk: consecutive slices of one
+// (t, i2) run, so every slice of it has the same B = G2[t][i2], which is staged in LDS
+// once per chunk (rows padded by one float, so reads across a's take distinct banks)
+// when it fits.  Per slice: A staged; C recomputed, or reloaded from the checkpoint of
+// the prefix group; the slice's rows in batches whose dE rows are staged together: dD
+// per row into the row's partial, the rows' dC summed; then dA and dC into the slice's
+// partials.  No two blocks write one partial, and the fixed-order sums below turn the
+// partials into dG1 (over the slices of (t, i1)), dG2 (a product over the slices of
 // (t, i2)) and dG3 (over the rows of (t, i3)).
 // ---------------------------------------------------------------------------
 constexpr int BWD_LDS_FLOATS = 40448;  // dynamic LDS budget (158 KB of the 160 KB)
@@ -446,22 +444,20 @@ __device__ __forceinline__ float dot_strided(const float* x, int xs, const float
 
 struct GenericBwdPlan {
   int stage_b;  // B in LDS
-  int db_lds;   // dB summed over the chunk in LDS
   int rows;     // dE rows per batch
   size_t lds_floats;
 };
 
 static GenericBwdPlan generic_bwd_plan(const Shape& s) {
   GenericBwdPlan pl;
-  const size_t nC = (size_t)s.d1 * s.d2 * s.R, nB = (size_t)s.R * s.d2 * s.R;
+  const size_t nC = (size_t)s.d1 * s.d2 * s.R;
   const size_t bs = (size_t)s.R * (s.d2 * s.R + 1);
   int rows = BWD_DE_FLOATS / s.D;
   rows = rows < 1 ? 1 : (rows > SLICE_ROWS ? SLICE_ROWS : rows);
   pl.rows = rows;
   const size_t base = 2 * nC + (size_t)s.d1 * s.R + (size_t)rows * s.D;
   pl.stage_b = base + bs <= (size_t)BWD_LDS_FLOATS;
-  pl.db_lds = base + (pl.stage_b ? bs : 0) + nB <= (size_t)BWD_LDS_FLOATS;
-  pl.lds_floats = base + (pl.stage_b ? bs : 0) + (pl.db_lds ? nB : 0);
+  pl.lds_floats = base + (pl.stage_b ? bs : 0);
   return pl;
 }
 
@@ -476,9 +472,9 @@ __global__ void __launch_bounds__(BWD_THREADS) k_bwd_generic(ShapeArgs s, const 
                                                              const uint32_t* __restrict__ run_base,
                                                              const int32_t* __restrict__ uniq_i3,
                                                              int32_t* __restrict__ ctr, const float* __restrict__ dE,
-                                                             float* __restrict__ dApart, float* __restrict__ dBpart,
+                                                             float* __restrict__ dApart, float* __restrict__ dCpart,
                                                              float* __restrict__ dDpart, float* __restrict__ ckpt,
-                                                             int32_t* __restrict__ ckpt_tag, int stage_b, int db_lds,
+                                                             int32_t* __restrict__ ckpt_tag, int stage_b,
                                                              int rows_per_batch) {
   extern __shared__ float lds[];
   const int d2R = s.d2 * s.R;
@@ -490,11 +486,13 @@ __global__ void __launch_bounds__(BWD_THREADS) k_bwd_generic(ShapeArgs s, const 
   float* As = dCs + nC;                    // d1 * R
   float* dEb = As + s.d1 * s.R;            // rows_per_batch * D
   float* Bs = dEb + rows_per_batch * s.D;  // R * (d2R + 1) when stage_b
-  float* dBs = Bs + (stage_b ? s.R * bp : 0);  // nB when db_lds
   __shared__ int s_chunk, s_flag;
   const int nsl = ctr[C_NSLICES];
   const int nchunks = (int)run_base[s.T * s.n2];
-  Worker worker = make_worker(SCHED_NQ, 1, 0);
+  __shared__ int left_behind;
+  if (threadIdx.x == 0) left_behind = 0;
+  __syncthreads();
+  Worker worker = make_worker(SCHED_NQ, 1, 0, &left_behind);
   int next = share_lo(nchunks, (int)gridDim.x, (int)blockIdx.x);
   int cur_pg = -1;
   const int rows12 = s.d1 * s.d2;
@@ -512,15 +510,12 @@ __global__ void __launch_bounds__(BWD_THREADS) k_bwd_generic(ShapeArgs s, const 
     const int run = ch.z;  // t * n2 + i2
     const int t = run / s.n2;
     const float* Bg = G2 + (int64_t)run * nB;
-    float* g2 = dBpart + (int64_t)c * nB;  // this chunk's dB partial
-    __syncthreads();  // the previous chunk is done with Bs and dBs
+    __syncthreads();  // the previous chunk is done with Bs
     if (stage_b) {
       StepQR ix(threadIdx.x, BWD_THREADS, d2R);
       for (int o = threadIdx.x; o < nB; o += BWD_THREADS, ix.next()) Bs[ix.q * bp + ix.r] = Bg[o];
     }
     const float* Bm = stage_b ? Bs : Bg;
-    if (db_lds)
-      for (int o = threadIdx.x; o < nB; o += BWD_THREADS) dBs[o] = 0.f;
     for (int si = s0; si < s1; ++si) {
       const int4 sl = slices[si];
       const int p = sl.x, rb = sl.y, re = sl.z;
@@ -580,8 +575,7 @@ __global__ void __launch_bounds__(BWD_THREADS) k_bwd_generic(ShapeArgs s, const 
         }
         __syncthreads();
       }
-      // dA = (sum dC) B^T  (d1 x R), dB = A^T (sum dC)  (R x d2R)
-      // dA: four consecutive lanes per output, each over every fourth term, combined by
+      // dA = (sum dC) B^T  (d1 x R): four consecutive lanes per output, each over every fourth term, combined by
       // shuffles within the wave (the loop runs whole block strides so every lane takes
       // part in the shuffles)
       float* g1 = dApart + (int64_t)si * s.d1 * s.R;  // this slice's dA partial
@@ -597,20 +591,10 @@ __global__ void __launch_bounds__(BWD_THREADS) k_bwd_generic(ShapeArgs s, const 
         v += __shfl_xor(v, 2, 64);
         if (ok && part == 0) g1[o] = v;
       }
-      StepQR dbx(threadIdx.x, BWD_THREADS, d2R);  // (a, column)
-      for (int o = threadIdx.x; o < nB; o += BWD_THREADS, dbx.next()) {
-        const int a = dbx.q, cc = dbx.r;
-        float acc = 0.f;
-        for (int j1 = 0; j1 < s.d1; ++j1) acc = fmaf(As[j1 * s.R + a], dCs[j1 * d2R + cc], acc);
-        // each thread owns its elements across the chunk's slices
-        if (db_lds)
-          dBs[o] += acc;
-        else
-          g2[o] = si == s0 ? acc : g2[o] + acc;
-      }
+      // the slice's dC, from which dG2 is formed (not kept with two cores)
+      if (dCpart)
+        for (int o = threadIdx.x; o < nC; o += BWD_THREADS) dCpart[(int64_t)si * nC + o] = dCs[o];
     }
-    if (db_lds)
-      for (int o = threadIdx.x; o < nB; o += BWD_THREADS) g2[o] = dBs[o];
   }
 }
 
@@ -683,27 +667,6 @@ __global__ void __launch_bounds__(GRED_THREADS) k_gred_g1(ShapeArgs s, const uin
   if (col) put_g(dG1, (int64_t)ti1 * d1R + e, sum8(a), lr, update);
 }
 
-// dG2[t][i2] = sum of the dB partials of the chunks of run (t, i2), in chunk order
-__global__ void __launch_bounds__(GRED_THREADS) k_gred_g2(const uint32_t* __restrict__ run_base,
-                                                          const float* __restrict__ dBpart, int nB,
-                                                          float* __restrict__ dG2, float lr, bool update) {
-  const int r = blockIdx.x;
-  const int e = blockIdx.y * GRED_THREADS + threadIdx.x;
-  if (e >= nB) return;
-  const int c0 = (int)run_base[r], c1 = (int)run_base[r + 1];
-  float a[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  int c = c0;
-  for (; c + 8 <= c1; c += 8) {
-    float v[8];
-#pragma unroll
-    for (int q = 0; q < 8; ++q) v[q] = dBpart[(int64_t)(c + q) * nB + e];
-#pragma unroll
-    for (int q = 0; q < 8; ++q) a[q] += v[q];
-  }
-  for (; c < c1; ++c) a[0] += dBpart[(int64_t)c * nB + e];
-  put_g(dG2, (int64_t)r * nB + e, sum8(a), lr, update);
-}
-
 // Sort keys t n3 + i3 of the unique rows (positions from U on get `sentinel`, which
 // sorts last), values = row ids
 __global__ void k_g3_keys(ShapeArgs s, const uint32_t* __restrict__ uniq_key, const int32_t* __restrict__ ctr, int n,
@@ -763,14 +726,13 @@ static int bits_of(uint64_t x) {
   return b;
 }
 
-// The three segment sums of the generic backward (M sorted occurrences bound the rows).
-// The segment sums of the generic and R = 64 paths.  After the R = 64 MFMA backward
-// (dg2_from_dc), dG2 comes from the per-slice dC partials by a product with G1, which
-// runs before the dG1 sums: with `update` those overwrite G1.
-static hipError_t launch_generic_reduce(const Shape& s, const Work& w, int64_t M, const float* G1, float* dG1,
-                                        float* dG2, float* dG3, float lr, bool update, bool dg2_from_dc,
-                                        hipStream_t st) {
-  const int d1R = s.d1 * s.R, nB = s.R * s.d2 * s.R, RD = s.R * s.d3;
+// The segment sums over the partials of every backward but the R = 32 one (M sorted
+// occurrences bound the rows).  dG2 comes from the per-slice dC partials by a product with
+// G1, which runs before the dG1 sums: with `update` those overwrite G1.  With two cores the
+// middle core is the identity and has no gradient.
+static hipError_t launch_partial_sums(const Shape& s, const Work& w, int64_t M, const float* G1, float* dG1,
+                                      float* dG2, float* dG3, float lr, bool update, hipStream_t st) {
+  const int d1R = s.d1 * s.R, RD = s.R * s.d3;
   const int n = (int)M;
   const uint32_t nbins = (uint32_t)s.T * (uint32_t)s.n3;
   hipLaunchKernelGGL(k_g3_keys, dim3((n + 255) / 256 < 4096 ? (n + 255) / 256 : 4096), dim3(256), 0, st,
@@ -786,13 +748,14 @@ static hipError_t launch_generic_reduce(const Shape& s, const Work& w, int64_t M
   hipLaunchKernelGGL(k_gred_g3, dim3(nbins, (RD + GRED_THREADS - 1) / GRED_THREADS), dim3(GRED_THREADS), 0, st,
                      (const int32_t*)w.g3lo, (const int32_t*)w.g3hi, (const uint32_t*)w.g3vals[res],
                      (const float*)w.dDpart, RD, dG3, lr, update);
-  if (dg2_from_dc && (e = launch_dg2_r64(s, w, G1, dG2, lr, update, st)) != hipSuccess) return e;
+  if (s.L != 2) {
+    e = bwd_r64_supported(s, w.M) ? launch_dg2_r64(s, w, G1, dG2, lr, update, st)
+                                  : launch_dg2_any(s, w, G1, dG2, lr, update, st);
+    if (e != hipSuccess) return e;
+  }
   hipLaunchKernelGGL(k_gred_g1, dim3(s.T * s.n1, (d1R + GRED_THREADS - 1) / GRED_THREADS), dim3(GRED_THREADS), 0, st,
                      shape_args(s), (const uint32_t*)w.dense_cnt, (const uint32_t*)w.dense_base,
                      (const float*)w.dApart, dG1, lr, update);
-  if (!dg2_from_dc)
-    hipLaunchKernelGGL(k_gred_g2, dim3(s.T * s.n2, (nB + GRED_THREADS - 1) / GRED_THREADS), dim3(GRED_THREADS), 0,
-                       st, (const uint32_t*)w.run_nch, (const float*)w.dBpart, nB, dG2, lr, update);
   return hipGetLastError();
 }
 
@@ -837,35 +800,38 @@ hipError_t launch_backward(const Shape& s, const Work& w, const float* G1, const
   if (bwd_r64_supported(s, w.M)) {  // MFMA partials, then the same segment sums (dG2 by a product)
     if (!w.dCpart) return hipErrorInvalidValue;
     if ((e = launch_bwd_r64(s, w, G1, G2, G3, prof, st)) != hipSuccess) return e;
-    return launch_generic_reduce(s, w, M, G1, dG1, dG2, dG3, lr, update, true, st);
+    return launch_partial_sums(s, w, M, G1, dG1, dG2, dG3, lr, update, st);
   }
   const int grid = persistent_grid() * 2;
   if ((e = fill_u32(reinterpret_cast<uint32_t*>(w.ctr + C_BWD_CTR), SCHED_NQ * SCHED_STRIDE, 0u, st)) != hipSuccess)
     return e;
+  if (s.sched != SCHED_STEAL_CKPT) {
+    if ((e = launch_bwd_any(s, w, G1, G2, G3, prof, st)) != hipSuccess) return e;
+    return launch_partial_sums(s, w, M, G1, dG1, dG2, dG3, lr, update, st);
+  }
   const GenericBwdPlan pl = generic_bwd_plan(s);
   const size_t lds = sizeof(float) * pl.lds_floats;
   const bool wide = (int64_t)s.d1 * s.d2 * s.R >= 1024 || s.D >= 128;
   const void* kfn = wide ? (const void*)k_bwd_generic<1024> : (const void*)k_bwd_generic<256>;
   if ((e = hipFuncSetAttribute(kfn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds)) != hipSuccess) return e;
-  if (s.sched == SCHED_STEAL_CKPT) {  // the forward's checkpoints may hold other cores' C
-    if (!w.ckpt_tag) return hipErrorInvalidValue;
-    if ((e = fill_u32(reinterpret_cast<uint32_t*>(w.ckpt_tag), CKPT_SLOTS, (uint32_t)CKPT_EMPTY, st)) != hipSuccess)
-      return e;
-  }
+  // the forward's checkpoints may hold other cores' C
+  if (!w.ckpt_tag) return hipErrorInvalidValue;
+  if ((e = fill_u32(reinterpret_cast<uint32_t*>(w.ckpt_tag), CKPT_SLOTS, (uint32_t)CKPT_EMPTY, st)) != hipSuccess)
+    return e;
   prof_begin(prof, K_BWD_FUSED, st);
   if (wide)
     hipLaunchKernelGGL(k_bwd_generic<1024>, dim3(grid), dim3(1024), lds, st, shape_args(s), G1, G2, G3,
                        (const int4*)w.slices, (const int4*)w.chunks, (const uint32_t*)w.run_nch,
-                       (const int32_t*)w.uniq_i3, w.ctr, (const float*)dE, w.dApart, w.dBpart, w.dDpart, w.ckpt,
-                       w.ckpt_tag, pl.stage_b, pl.db_lds, pl.rows);
+                       (const int32_t*)w.uniq_i3, w.ctr, (const float*)dE, w.dApart, w.dCpart, w.dDpart, w.ckpt,
+                       w.ckpt_tag, pl.stage_b, pl.rows);
   else
     hipLaunchKernelGGL(k_bwd_generic<256>, dim3(grid), dim3(256), lds, st, shape_args(s), G1, G2, G3,
                        (const int4*)w.slices, (const int4*)w.chunks, (const uint32_t*)w.run_nch,
-                       (const int32_t*)w.uniq_i3, w.ctr, (const float*)dE, w.dApart, w.dBpart, w.dDpart, w.ckpt,
-                       w.ckpt_tag, pl.stage_b, pl.db_lds, pl.rows);
+                       (const int32_t*)w.uniq_i3, w.ctr, (const float*)dE, w.dApart, w.dCpart, w.dDpart, w.ckpt,
+                       w.ckpt_tag, pl.stage_b, pl.rows);
   prof_end(prof, K_BWD_FUSED, st);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  return launch_generic_reduce(s, w, M, G1, dG1, dG2, dG3, lr, update, false, st);
+  return launch_partial_sums(s, w, M, G1, dG1, dG2, dG3, lr, update, st);
 }
 
 // ---------------------------------------------------------------------------

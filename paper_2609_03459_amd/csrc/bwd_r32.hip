@@ -83,7 +83,7 @@ __global__ void __launch_bounds__(64 * BW_WAVES, 1)
               const int4* __restrict__ chunks, const uint32_t* __restrict__ run_base,
               const int32_t* __restrict__ uniq_i3, int32_t* __restrict__ ctr, float* __restrict__ dApart,
               float* __restrict__ dBpart, float* __restrict__ g3part, int nsl_cap, int nch_cap) {
-  extern __shared__ float lds[];
+  extern __shared__ __align__(16) float lds[];  // all of the LDS at n3 = 252: no static array beside it
   const int lane = lane_id();
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   constexpr int GR = 16 / D3;     // rows per group
@@ -132,7 +132,7 @@ __global__ void __launch_bounds__(64 * BW_WAVES, 1)
   const buf_t g3buf = make_buf(G3t, (uint32_t)s.n3 * (128u * D3));
 
   // one queue per owner; its workgroups are blocks q, q + nq, ... of the grid
-  Worker worker = {1, 0, wave * (int)(gridDim.x / nq) + (int)(blockIdx.x / nq), (int)(gridDim.x / nq), BW_WAVES, 0, true};
+  Worker worker = {1, 0, wave * (int)(gridDim.x / nq) + (int)(blockIdx.x / nq), (int)(gridDim.x / nq), BW_WAVES, nullptr, true};
   int cur_run = -1;
   float Bop[32];   // stage-1 B operand B_h[a = 4 s + l4][16 nt + l15], (s, nt) -> 4 s + nt
   float BTop[32];  // dA B operand B_h^T[(j2 = l4, b' = s)][a = 16 nt2 + l15], (s, nt2) -> 16 nt2 + s

@@ -36,7 +36,7 @@ __global__ void __launch_bounds__(64 * B64_WAVES, B64_WG_PER_CU)
               const int4* __restrict__ chunks, const uint32_t* __restrict__ run_base,
               const int32_t* __restrict__ uniq_i3, int32_t* __restrict__ ctr, float* __restrict__ dApart,
               float* __restrict__ dCpart, float* __restrict__ dDpart) {
-  __shared__ float scr_all[B64_WAVES * B64_SCR];
+  __shared__ __align__(16) float scr_all[B64_WAVES * B64_SCR];
   const int lane = lane_id();
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   float* scr = scr_all + wave * B64_SCR;
@@ -59,7 +59,10 @@ __global__ void __launch_bounds__(64 * B64_WAVES, B64_WG_PER_CU)
   // LDS tile: stage-1 write of (slice l4, row 4 r + j2, column b = 16 (nt & 3) + l15)
   const int wr_base = l4 * B64_SLICE + l15;
 
-  Worker worker = make_worker(SCHED_NQ, B64_WAVES, wave);
+  __shared__ int left_behind;
+  if (threadIdx.x == 0) left_behind = 0;
+  __syncthreads();
+  Worker worker = make_worker(SCHED_NQ, B64_WAVES, wave, &left_behind);
   const int wid = blockIdx.x * B64_WAVES + wave, nw = gridDim.x * B64_WAVES;
   int st_next = share_lo(nch, nw, wid);
   const int st_hi = share_lo(nch, nw, wid + 1);

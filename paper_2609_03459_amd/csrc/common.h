@@ -26,7 +26,7 @@ struct Shape {
   int slice_rows;  // rows per work slice: SLICE_ROWS, or 1 when prefix reuse is off (ablation)
   int dedup;       // 1: exact dedup of rows; 0: every occurrence is its own row (ablation)
   int sched;       // work distribution: SCHED_STEAL, SCHED_STATIC, SCHED_STEAL_CKPT or SCHED_GROUP (ablation)
-  int chunk_slices;  // slices per chunk of one (t, i2) run (TTEMB_CHUNK, or TTEMB_R64_CHUNK at R = 64)
+  int chunk_slices;  // slices per chunk of one (t, i2) run (TTEMB_CHUNK, or TTEMB_R64_CHUNK)
   // Number of TT cores and their factors.  The fields above are the three-factor
   // view that the grouping and the fused kernels work on: for L = 3 the cores
   // themselves; for L >= 4 (n1, d1) = products of the factors of cores 0..L-3,
@@ -104,13 +104,12 @@ struct Work {
   int32_t* slice_i1;      // [nsl_max] first digit i1 of each slice's group
   uint32_t* run_nch;      // [T*n2 + 1] chunks per (t, i2) run, then their exclusive scan
   int4* chunks;           // [nch_max] (first slice, slice count, run, 0)
-  float* dApart;          // backward: dA of each slice, [2][nsl_max][d1*R] (MFMA: one per rank half) or
-                          // [nsl_max][d1*R] (generic)
-  float* dBpart;          // backward: dB of each chunk, [2][nch_max][R*d2*R/2] (R = 32 MFMA) or [nch_max][R*d2*R]
-                          // (generic); null on the R = 64 MFMA path, which keeps dCpart instead
-  float* dCpart;          // R = 64 MFMA backward: dC sum of each slice, [nsl_max][d1][d2*R]
+  float* dApart;          // backward: dA of each slice, [2][nsl_max][d1*R] (R = 32 MFMA: one per rank half) or
+                          // [nsl_max][d1*R]
+  float* dBpart;          // R = 32 MFMA backward: dB of each chunk, [2][nch_max][R*d2*R/2]; else null
+  float* dCpart;          // every other backward: dC sum of each slice, [nsl_max][d1][d2*R]; null for two cores
   float* g3part;          // [MAX_BWD_WG][n3*R*d3/2] backward: dG3 half of each workgroup
-  // generic backward (shapes the MFMA backward does not serve), else null: partials of
+  // backward of the shapes the R = 32 MFMA backward does not serve, else null: partials of
   // the fixed-order segment sums and the (table, i3) order of the unique rows
   float* dDpart;          // [M][R*d3] dD of each unique row
   uint32_t* g3keys[2];    // [M] sort keys t*n3 + i3 of the unique rows (ping-pong)
@@ -196,6 +195,15 @@ bool fwd_r64_supported(const Shape& s, int64_t max_indices);
 hipError_t sort_pairs(const Work& w, uint32_t* const keys[2], uint32_t* const vals[2], int n, int key_bits,
                       int* out, hipStream_t st);
 
+// The kernels of any shape (any.hip).
+int any_stack_slices(const Shape& s);
+hipError_t launch_fwd_any(const Shape& s, const Work& w, const float* G1, const float* G2, const float* G3,
+                          const Prof& prof, hipStream_t st);
+hipError_t launch_bwd_any(const Shape& s, const Work& w, const float* G1, const float* G2, const float* G3,
+                          const Prof& prof, hipStream_t st);
+hipError_t launch_dg2_any(const Shape& s, const Work& w, const float* G1, float* dG2, float lr, bool update,
+                          hipStream_t st);
+
 // Small generic kernels shared across units (defined in group.hip).
 hipError_t fill_u32(uint32_t* p, int64_t n, uint32_t v, hipStream_t st);
 hipError_t fill_f32(float* p, int64_t n, float v, hipStream_t st);
@@ -280,9 +288,10 @@ __device__ __forceinline__ float2 ntl2(const float2* p) {
 // of its own.  A worker takes one chunk of its home queue by its rank there, without
 // an atomic, then claims the following ones with a single atomic each (consecutive
 // chunks, so neighbouring groups stay in the home XCD's L2); once the home queue is
-// empty it steals from the following queues in turn.  An empty queue is never visited
-// again, and one that was dealt out by rank never asked, so a worker makes at most nq
-// failed claims before it exits, and none in a launch with no more chunks than workers.
+// empty it steals from the following queues in turn.  A queue that a worker finds empty is
+// not visited again by any worker of its block, and one that was dealt out by rank never
+// asked, so a block makes few more than nq failed claims before it exits, and none in a
+// launch with no more chunks than workers.
 // The forward uses one queue per XCD (workgroup blockIdx % 8 runs on XCD blockIdx % 8); the specialised backward
 // gives every (table, rank half) owner one queue, since its LDS accumulator is its own.
 //
@@ -295,42 +304,51 @@ constexpr int SCHED_STRIDE = 32;  // ints between queue counters (128 bytes)
 
 __device__ __forceinline__ int share_lo(int nchunks, int W, int v) { return (int)(((int64_t)nchunks * v) / W); }
 
-// A worker's place in the queues: nq queues; its home and rank there; how many queues it
-// has left behind; the workers whose home is queue v, which took its first chunks by rank:
+// A worker's place in the queues: nq queues; its home and rank there; the workers whose home is queue v, which took its first chunks by rank:
 // blocks v, v + nq, ... of nb, `per` workers each.  Ranks go through the blocks first, so
-// that few chunks spread over as many CUs as there are.
+// that few chunks spread over as many CUs as there are.  left_behind (in LDS, zero at first,
+// one per block) counts the queues, in turn from home, that a worker of the block found empty;
+// null with a single queue.
 struct Worker {
-  int nq, home, rank, nb, per, cursor;
+  int nq, home, rank, nb, per;
+  int* left_behind;
   bool fresh;  // the chunk by rank is still to be taken
 };
 __device__ __forceinline__ int queue_blocks(int nb, int nq, int v) { return nb > v ? (nb - 1 - v) / nq + 1 : 0; }
-__device__ __forceinline__ Worker make_worker(int nq, int per, int w) {
+__device__ __forceinline__ Worker make_worker(int nq, int per, int w, int* left_behind) {
   const int home = (int)blockIdx.x % nq;
-  return Worker{nq, home, w * queue_blocks((int)gridDim.x, nq, home) + (int)blockIdx.x / nq, (int)gridDim.x, per, 0, true};
+  return Worker{nq, home, w * queue_blocks((int)gridDim.x, nq, home) + (int)blockIdx.x / nq, (int)gridDim.x, per, left_behind, true};
 }
 
 __device__ __forceinline__ int claim_queues(int32_t* q, int nchunks, Worker* k) {
-  while (k->cursor < k->nq) {
-    int v = k->home + k->cursor;
+  if (k->fresh) {
+    k->fresh = false;
+    const int c = share_lo(nchunks, k->nq, k->home) + k->rank;
+    if (c < share_lo(nchunks, k->nq, k->home + 1)) return c;
+  }
+  int cursor = 0;
+  if (k->left_behind)
+    cursor = __builtin_amdgcn_readfirstlane(__hip_atomic_load(k->left_behind, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
+  while (cursor < k->nq) {
+    int v = k->home + cursor;
     if (v >= k->nq) v -= k->nq;
     const int hi = share_lo(nchunks, k->nq, v + 1);
-    if (k->fresh) {  // v is the home queue
-      k->fresh = false;
-      const int c = share_lo(nchunks, k->nq, v) + k->rank;
-      if (c < hi) return c;
-    } else {
-      const int lo = share_lo(nchunks, k->nq, v) + queue_blocks(k->nb, k->nq, v) * k->per;
-      if (lo < hi) {
-        int c = -1;
-        if (lane_id() == 0) {
-          const int got = lo + atomicAdd(&q[v * SCHED_STRIDE], 1);
-          if (got < hi) c = got;
-        }
-        c = __builtin_amdgcn_readfirstlane(c);
-        if (c >= 0) return c;
+    const int lo = share_lo(nchunks, k->nq, v) + queue_blocks(k->nb, k->nq, v) * k->per;
+    if (lo < hi) {
+      int c = -1;
+      if (lane_id() == 0) {
+        const int got = lo + atomicAdd(&q[v * SCHED_STRIDE], 1);
+        if (got < hi) c = got;
       }
+      c = __builtin_amdgcn_readfirstlane(c);
+      if (c >= 0) return c;
     }
-    ++k->cursor;
+    int next = cursor + 1;
+    if (k->left_behind && lane_id() == 0) {
+      const int other = __hip_atomic_fetch_max(k->left_behind, next, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      next = other > next ? other : next;
+    }
+    cursor = __builtin_amdgcn_readfirstlane(next);
   }
   return -1;
 }

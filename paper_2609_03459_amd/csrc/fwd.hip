@@ -3,6 +3,7 @@
 //                  once in LDS and reused for every row: E_u = C.D_u
 //   pooling      : V[bag] = sum of E over the bag's occurrences, in order
 // Slices come in (table, i2, i1) order so consecutive groups share G2[i2].
+#include "any.h"
 #include "common.h"
 
 namespace ttemb {
@@ -72,7 +73,10 @@ __global__ void __launch_bounds__(FWD_THREADS) k_fwd_generic(ShapeArgs s, const 
   // work units: FWD_CHUNK consecutive slices, or with SCHED_GROUP the chunk list's whole groups
   const bool by_group = s.sched == SCHED_GROUP;
   const int nchunks = by_group ? (int)run_base[s.T * s.n2] : (nsl + FWD_CHUNK - 1) / FWD_CHUNK;
-  Worker worker = make_worker(SCHED_NQ, 1, 0);
+  __shared__ int left_behind;
+  if (threadIdx.x == 0) left_behind = 0;
+  __syncthreads();
+  Worker worker = make_worker(SCHED_NQ, 1, 0, &left_behind);
   int next = share_lo(nchunks, (int)gridDim.x, (int)blockIdx.x);
   int cur_pg = -1, cur_run = -1;
   const float* Bm = G2;
@@ -173,7 +177,7 @@ __global__ void __launch_bounds__(64 * F32_WAVES, F32_WG_PER_CU)
               const int4* __restrict__ slices, const int32_t* __restrict__ slice_i1,
               const int4* __restrict__ chunks, const uint32_t* __restrict__ run_base,
               const int32_t* __restrict__ uniq_i3, int32_t* __restrict__ ctr, float* __restrict__ E) {
-  __shared__ float scr_all[F32_WAVES * F32_SCR];
+  __shared__ __align__(16) float scr_all[F32_WAVES * F32_SCR];
   const int lane = lane_id();
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   float* scr = scr_all + wave * F32_SCR;
@@ -202,7 +206,10 @@ __global__ void __launch_bounds__(64 * F32_WAVES, F32_WG_PER_CU)
   const uint32_t vo_e = D3 == 8 ? 4u * (uint32_t)((l4 >> 1) * 128 + l15 * 8 + 4 * (l4 & 1))
                                 : 4u * (uint32_t)(2 * l4 * DW + l15 * 2);
 
-  Worker worker = make_worker(SCHED_NQ, F32_WAVES, wave);
+  __shared__ int left_behind;
+  if (threadIdx.x == 0) left_behind = 0;
+  __syncthreads();
+  Worker worker = make_worker(SCHED_NQ, F32_WAVES, wave, &left_behind);
   int cur_run = -1;
   float Bop[64];  // B[a = 4 s + l4][16 nt + l15], (s, nt) -> 8 s + nt
 
@@ -531,7 +538,7 @@ __global__ void __launch_bounds__(64 * F64_WAVES, F64_WG_PER_CU)
               const int4* __restrict__ slices, const int32_t* __restrict__ slice_i1,
               const int4* __restrict__ chunks, const uint32_t* __restrict__ run_base,
               const int32_t* __restrict__ uniq_i3, int32_t* __restrict__ ctr, float* __restrict__ E) {
-  __shared__ float scr_all[F64_WAVES * F64_SCR];
+  __shared__ __align__(16) float scr_all[F64_WAVES * F64_SCR];
   const int lane = lane_id();
   // E rows of all unique rows beyond the last-level cache: stored non-temporally
   const bool e_nt = (uint64_t)(uint32_t)ctr[C_U] * 512u > STREAM_BYTES;
@@ -551,7 +558,10 @@ __global__ void __launch_bounds__(64 * F64_WAVES, F64_WG_PER_CU)
   const int wr_base = l4 * F64_SLICE + l15;
   const int rd_base = l15 * F64_PITCH + 16 * l4;
 
-  Worker worker = make_worker(SCHED_NQ, F64_WAVES, wave);
+  __shared__ int left_behind;
+  if (threadIdx.x == 0) left_behind = 0;
+  __syncthreads();
+  Worker worker = make_worker(SCHED_NQ, F64_WAVES, wave, &left_behind);
   int c_rb = 0, c_nr = 0, c_i1 = 0;
   int f = 0, ns = 0, run = -1, t = 0, qd = 0;
   int c = -1;
@@ -958,6 +968,10 @@ hipError_t launch_forward(const Shape& s, const Work& w, const float* G1, const 
       prof_end(prof, K_FWD_FUSED, st);
       e = hipGetLastError();
       if (e != hipSuccess) return e;
+      return launch_pool(s, w.E, w.inv, offsets, M, B, out, prof, st);
+    }
+    if (s.sched != SCHED_STEAL_CKPT) {
+      if ((e = launch_fwd_any(s, w, G1, G2, G3, prof, st)) != hipSuccess) return e;
       return launch_pool(s, w.E, w.inv, offsets, M, B, out, prof, st);
     }
     const size_t nC = (size_t)s.d1 * s.d2 * s.R, nA = (size_t)s.d1 * s.R;

@@ -110,13 +110,11 @@ static size_t layout(const Shape& s, int64_t M, int64_t B, char* base, Work* w, 
   // --- regions of the backward only ---
   W->seg_part = (float*)take(4 * (size_t)nseg * 2 * s.D);
   W->sorted_bag = (int32_t*)take(4 * m);
-  // gradient partials: the MFMA backward's rank halves, or the generic backward's
-  // per-slice dA, per-chunk dB and per-row dD with the (t, i3) order of the rows
+  // gradient partials: the R = 32 MFMA backward's rank halves, or the other backwards'
+  // per-slice dA and dC and per-row dD with the (t, i3) order of the rows
   W->dApart = (float*)take(4 * (size_t)(bwd_r32 ? 2 : 1) * nsl_max * s.d1 * s.R);
-  // the R = 64 MFMA backward keeps each slice's dC sum instead of a dB per chunk
-  const bool bwd_r64 = !bwd_r32 && bwd_r64_supported(s, m);
-  W->dBpart = bwd_r64 ? nullptr : (float*)take(4 * (size_t)nch_max * s.R * s.d2 * s.R);
-  W->dCpart = bwd_r64 ? (float*)take(4 * (size_t)nsl_max * s.d1 * s.d2 * s.R) : nullptr;
+  W->dBpart = bwd_r32 ? (float*)take(4 * (size_t)nch_max * s.R * s.d2 * s.R) : nullptr;
+  W->dCpart = bwd_r32 || s.L == 2 ? nullptr : (float*)take(4 * (size_t)nsl_max * s.d1 * s.d2 * s.R);
   W->g3part = bwd_r32 ? (float*)take(4 * (size_t)MAX_BWD_WG * (s.n3 * s.R * s.d3 / 2)) : nullptr;
   W->dDpart = bwd_r32 ? nullptr : (float*)take(4 * (size_t)m * s.R * s.d3);
   for (int k = 0; k < 2; ++k) {
@@ -173,6 +171,14 @@ static bool al(const void* p, uintptr_t a) { return ((uintptr_t)p & (a - 1)) == 
 // SLICE_ROWS.
 static int prefix_slice_rows(const Shape& s) {
   return s.R == 64 && s.d1 == 4 && s.d2 == 4 && s.d3 == 8 ? 16 : SLICE_ROWS;
+}
+
+// Slices per chunk: 32 where the matrix-core kernels of R = 32 keep B in registers over a
+// chunk (TTEMB_CHUNK), one quad on the R = 64 shape, four for the kernels of any shape,
+// which keep nothing between stacks.
+static int view_chunk_slices(const Shape& s) {
+  const bool d44 = s.d1 == 4 && s.d2 == 4;
+  return s.R == 32 && d44 && (s.d3 == 8 || s.d3 == 2) ? TTEMB_CHUNK : TTEMB_R64_CHUNK;
 }
 
 static int bit_length(uint64_t x) {
@@ -235,7 +241,7 @@ static tt_emb_status create_view(const tt_emb_desc* d, int L, const int32_t* nk,
   s.slice_rows = prefix_slice_rows(s);
   s.dedup = 1;
   s.sched = SCHED_STEAL;
-  s.chunk_slices = s.R == 64 ? TTEMB_R64_CHUNK : TTEMB_CHUNK;
+  s.chunk_slices = view_chunk_slices(s);
   s.L = L;
   for (int k = 0; k < MAX_CORES; ++k) {
     s.nk[k] = k < L ? nk[k] : 1;

@@ -51,3 +51,39 @@ def test_chunks_by_rank_and_by_claim(lib, orc, runs):
     # owner), exactly as many, and a few more, so that chunks are taken by rank, claimed and stolen
     case = ttgen.tiny(8100 + runs % 97, 1, (2, runs, 2), (4, 4, 8), 32, B=3 * runs, single=True)
     _check(lib, orc, case, f"{runs} chunks")
+
+
+# Shapes without a specialised kernel, at the edges of the matrix tiles: one slice, several or
+# none-filling slices to a 16-row stack (d1 = 1 .. 17), C of one 16-row tile and of several
+# (d1 d2 = 1, 16, 20, 34), ranks at, below and past 16, 32 and 64, and every way a tile of 16
+# (row, j3) items is cut (d3 = 1, 2, 3, 4, 5, 8, 16)
+ANY_SHAPES = [((1, 1, 1), 1), ((1, 4, 2), 16), ((2, 2, 4), 8), ((3, 1, 2), 32), ((2, 8, 4), 16), ((4, 4, 8), 16),
+              ((4, 2, 4), 64), ((4, 4, 4), 32), ((4, 4, 2), 64), ((5, 4, 8), 32), ((16, 1, 4), 16), ((17, 2, 3), 7),
+              ((2, 3, 5), 33), ((6, 2, 1), 64), ((3, 4, 16), 17), ((8, 2, 8), 64)]
+
+
+@pytest.mark.parametrize("sched", ["steal", "steal_ckpt", "group"])
+@pytest.mark.parametrize("d,R", ANY_SHAPES)
+def test_any_shape(lib, orc, d, R, sched):
+    # 900 rows of six prefixes per table, about half of them met: groups of three slices and
+    # more.  steal_ckpt keeps the vector-ALU kernels, so both paths are held to one oracle
+    case = ttgen.tiny(8200 + R, 2, (3, 2, 150), d, R, B=110, max_len=8, sigma=0.3)
+    _check(lib, orc, case, f"any {d} R={R} {sched}", sched=sched)
+
+
+@pytest.mark.parametrize("n,d,R", [((40, 30), (16, 8), 32), ((300, 2), (3, 5), 7), ((9, 200), (20, 4), 64)])
+def test_two_cores(lib, orc, n, d, R):
+    # the identity middle core is never multiplied: C is A and dA is dC
+    case = ttgen.tiny_n(8300 + R, 2, n, d, R, 90, max_len=9)
+    cores = [torch.from_numpy(c).cuda() for c in case["cores"]]
+    idx, off = torch.from_numpy(case["idx"]).cuda(), torch.from_numpy(case["offsets"]).cuda()
+    dV = torch.from_numpy(case["dV"]).cuda()
+    emb = lib.TTEmbedding(2, case["N"], n, d, R, max_indices=idx.numel(), max_bags=90)
+    V = emb.forward_n(cores, idx, off)
+    grads = emb.backward_n(cores, idx, off, dV)
+    torch.cuda.synchronize()
+    mag_case = dict(case, cores=[np.abs(c) for c in case["cores"]], dV=np.abs(case["dV"]))
+    assert_close(f"forward {n} {d}", V.cpu().numpy().reshape(180, -1), orc.forward_n(case)[0], orc.forward_n(mag_case)[0])
+    ref, mag = orc.backward_n(case)[0], orc.backward_n(mag_case)[0]
+    for k in range(2):
+        assert_close(f"dG{k + 1} {n} {d}", grads[k].cpu().numpy(), ref[k], mag[k])
