@@ -26,7 +26,9 @@ struct Shape {
   int slice_rows;  // rows per work slice: SLICE_ROWS, or 1 when prefix reuse is off (ablation)
   int dedup;       // 1: exact dedup of rows; 0: every occurrence is its own row (ablation)
   int sched;       // work distribution: SCHED_STEAL, SCHED_STATIC, SCHED_STEAL_CKPT or SCHED_GROUP (ablation)
-  int chunk_slices;  // slices per chunk of one (t, i2) run (TTEMB_CHUNK, or TTEMB_R64_CHUNK)
+  int chunk_slices;  // most slices per chunk of one (t, i2) run, and
+  int chunk_unit;    // fewest (chunk_slices a power-of-two multiple): chunk_len picks between them,
+  int chunk_target;  // the longest that still gives this many chunks
   // Number of TT cores and their factors.  The fields above are the three-factor
   // view that the grouping and the fused kernels work on: for L = 3 the cores
   // themselves; for L >= 4 (n1, d1) = products of the factors of cores 0..L-3,
@@ -65,16 +67,25 @@ constexpr int SCAN_THREADS = 256;
 constexpr int SCAN_ITEMS = 16;
 constexpr int SCAN_TILE = SCAN_THREADS * SCAN_ITEMS;
 constexpr int SLICE_ROWS = 32;   // unique rows per work slice
-constexpr int CHUNK_SLICES = 32; // most slices per chunk (one (t, i2) run); Shape::chunk_slices <= this
-// Slices per chunk at rank 64: the MFMA forward streams B from L2 for every quad
-// (nothing is kept per chunk), so short chunks cost no reloads and give the
-// persistent waves many more work units than there are waves.
-#ifndef TTEMB_R64_CHUNK
-#define TTEMB_R64_CHUNK 4
-#endif
-#ifndef TTEMB_CHUNK
-#define TTEMB_CHUNK 32
-#endif
+// Slices per chunk.  R = 32 matrix-core kernels: up to 32, since they keep B in registers
+// over a chunk and write a dB partial for it, at least one quad; R = 64: one quad (B streams
+// from L2 for every quad, so short chunks cost no reloads); kernels of any shape: one to
+// four stacks, which share nothing, so that longer chunks only save claims.
+constexpr int R32_CHUNK = 32, R64_CHUNK = 4, QUAD = 4, ANY_CHUNK_STACKS = 4;
+// A launch of few chunks per resident wave (2,048 to 6,144 of them) lasts as long as one
+// wave's last chunk, and one of many short chunks pays for claims and, at R = 32, for
+// reloads of B and dB partials.  Both sides, measured with chunk_len at targets of 4,096 /
+// 8,192 / 16,384 chunks: the 8-table R = 32 training steps (310k slices: 32-slice chunks at
+// the first two, 16 at the third) 1,880 / 1,878 / 1,934 us; the R = 32 forward over 95k
+// slices 118 / 108 / 120 us; d = (4, 4, 4), R = 16 over 150k slices, forward and backward
+// kernel, 98 + 137 / 105 + 139 / 128 + 159 us; and where 32-slice chunks had left most waves
+// idle, the d = (4, 4, 2), R = 32 forward of 6k slices 33 -> 13 us and its backward 44 -> 26.
+constexpr int R32_CHUNK_TARGET = 8192, ANY_CHUNK_TARGET = 4096;
+__host__ __device__ __forceinline__ uint32_t chunk_len(uint32_t nslices, int unit, int most, int target) {
+  uint32_t cs = (uint32_t)most;
+  while (cs > (uint32_t)unit && nslices / cs < (uint32_t)target) cs >>= 1;
+  return cs;
+}
 constexpr int SEG_CHUNK = 256;   // sorted occurrences per dE chunk
 constexpr int MAX_BWD_WG = 256;  // workgroups of the MFMA backward (one per CU on MI355X)
 
@@ -96,12 +107,12 @@ struct Work {
   int32_t* uniq_i3;       // [M] last digit i3 of each unique row
   int32_t* occ_start;     // [M+1] first sorted position of each unique row
   int32_t* pg_start;      // [M+1] first unique row of each prefix group
-  uint32_t* pg_key;       // [M] t*n1*n2 + i1*n2 + i2 of each group
+  uint32_t* pg_key;       // [M] t*n1*n2 + i1*n2 + i2 of each group (where the sort's spare keys were)
   uint32_t* dense_cnt;    // [ndense] slices per prefix slot, (t, i2, i1) order
   uint32_t* dense_base;   // [ndense] exclusive scan of dense_cnt
   int32_t* dense_pg;      // [ndense] group id per slot
   int4* slices;           // [nsl_max] (group, row_begin, row_end, key)
-  int32_t* slice_i1;      // [nsl_max] first digit i1 of each slice's group
+  int32_t* slice_i1;      // [nsl_max] first digit i1 of each slice's group (where the sort's spare positions were)
   uint32_t* run_nch;      // [T*n2 + 1] chunks per (t, i2) run, then their exclusive scan
   int4* chunks;           // [nch_max] (first slice, slice count, run, 0)
   float* dApart;          // backward: dA of each slice, [2][nsl_max][d1*R] (R = 32 MFMA: one per rank half) or

@@ -758,32 +758,44 @@ __global__ void k_make_slices_rows(const uint32_t* __restrict__ dense_base,
   }
 }
 
-// chunks of the specialised kernels: up to cs (the shape's chunk_slices) consecutive slices of
-// one (t, i2) run; run r covers slices [dense_base[r*n1], dense_base[(r+1)*n1])
+// chunks of the fused kernels: up to chunk_len consecutive slices of one (t, i2) run;
+// run r covers slices [dense_base[r*n1], dense_base[(r+1)*n1])
 __global__ void k_run_counts(const uint32_t* __restrict__ dense_base, const int32_t* __restrict__ ctr, int nruns,
-                             int n1, int cs, uint32_t* __restrict__ run_nch) {
+                             int n1, int unit, int most, int target, uint32_t* __restrict__ run_nch) {
   const int r = blockIdx.x * blockDim.x + threadIdx.x;
   if (r > nruns) return;
   if (r == nruns) {  // the scan turns this slot into the total
     run_nch[r] = 0;
     return;
   }
+  const uint32_t nsl = (uint32_t)ctr[C_NSLICES];
+  const uint32_t cs = chunk_len(nsl, unit, most, target);
   const uint32_t b0 = dense_base[(int64_t)r * n1];
-  const uint32_t b1 = r + 1 < nruns ? dense_base[(int64_t)(r + 1) * n1] : (uint32_t)ctr[C_NSLICES];
+  const uint32_t b1 = r + 1 < nruns ? dense_base[(int64_t)(r + 1) * n1] : nsl;
   run_nch[r] = (b1 - b0 + cs - 1) / cs;
 }
 
+// One thread per chunk: its run by binary search over the runs' first chunks (a run can
+// hold thousands of chunks, so a thread per run would write them out one by one: 100 us at
+// two cores, whose tables are one run each, against 4 us)
 __global__ void k_make_chunks(const uint32_t* __restrict__ dense_base, const uint32_t* __restrict__ run_base,
-                              const int32_t* __restrict__ ctr, int nruns, int n1, int cs, int4* __restrict__ chunks) {
-  const int r = blockIdx.x * blockDim.x + threadIdx.x;
-  if (r >= nruns) return;
-  const uint32_t b0 = dense_base[(int64_t)r * n1];
-  const uint32_t b1 = r + 1 < nruns ? dense_base[(int64_t)(r + 1) * n1] : (uint32_t)ctr[C_NSLICES];
-  const uint32_t c0 = run_base[r];
-  for (uint32_t k = 0; b0 + k * cs < b1; ++k) {
-    const uint32_t f = b0 + k * cs;
-    const uint32_t n = b1 - f < (uint32_t)cs ? b1 - f : (uint32_t)cs;
-    chunks[c0 + k] = make_int4((int)f, (int)n, r, 0);
+                              const int32_t* __restrict__ ctr, int nruns, int n1, int unit, int most, int target,
+                              int4* __restrict__ chunks) {
+  const uint32_t nsl = (uint32_t)ctr[C_NSLICES];
+  const uint32_t cs = chunk_len(nsl, unit, most, target);
+  const uint32_t nch = run_base[nruns];
+  for (uint32_t c = blockIdx.x * blockDim.x + threadIdx.x; c < nch; c += gridDim.x * blockDim.x) {
+    int lo = 0, hi = nruns;  // the last run whose first chunk does not come after c (never an empty one)
+    while (hi - lo > 1) {
+      const int mid = (lo + hi) >> 1;
+      if (run_base[mid] <= c)
+        lo = mid;
+      else
+        hi = mid;
+    }
+    const uint32_t b1 = lo + 1 < nruns ? dense_base[(int64_t)(lo + 1) * n1] : nsl;
+    const uint32_t f = dense_base[(int64_t)lo * n1] + (c - run_base[lo]) * cs;
+    chunks[c] = make_int4((int)f, (int)(b1 - f < cs ? b1 - f : cs), lo, 0);
   }
 }
 
@@ -815,13 +827,13 @@ __global__ void k_make_group_chunks(const uint32_t* __restrict__ dense_cnt, cons
 // k_run_counts and the scan of its counts in one workgroup when nruns + 1 <=
 // SCAN_TILE: chunk counts per run, exclusive scan into run_nch (the total at
 // run_nch[nruns] and in ctr[C_NCHUNKS]).  A thread owns SCAN_ITEMS consecutive
-// runs.  (The chunk list stays a launch of its own: a run can hold thousands of
-// chunks at the no-dedup level.)
+// runs.
 __global__ void __launch_bounds__(SCAN_THREADS) k_runs_one_block(const uint32_t* __restrict__ dense_base,
-                                                                 int32_t* __restrict__ ctr, int nruns, int n1, int cs,
-                                                                 uint32_t* __restrict__ run_nch) {
+                                                                 int32_t* __restrict__ ctr, int nruns, int n1,
+                                                                 int unit, int most, int target, uint32_t* __restrict__ run_nch) {
   __shared__ uint32_t smem[SCAN_THREADS / 64];
   const uint32_t nsl = (uint32_t)ctr[C_NSLICES];
+  const uint32_t cs = chunk_len(nsl, unit, most, target);
   const int r0 = (int)threadIdx.x * SCAN_ITEMS;
   uint32_t b[SCAN_ITEMS + 1], cnt[SCAN_ITEMS], sum = 0;
 #pragma unroll
@@ -1024,16 +1036,17 @@ hipError_t launch_group(const Shape& s, const Work& w, const int64_t* idx, int64
   }
   if (nruns + 1 <= SCAN_TILE) {
     hipLaunchKernelGGL(k_runs_one_block, dim3(1), dim3(SCAN_THREADS), 0, st, (const uint32_t*)w.dense_base, w.ctr,
-                       nruns, s.n1, s.chunk_slices, w.run_nch);
+                       nruns, s.n1, s.chunk_unit, s.chunk_slices, s.chunk_target, w.run_nch);
   } else {
     hipLaunchKernelGGL(k_run_counts, dim3((nruns + 1 + 255) / 256), dim3(256), 0, st, (const uint32_t*)w.dense_base,
-                       (const int32_t*)w.ctr, nruns, s.n1, s.chunk_slices, w.run_nch);
+                       (const int32_t*)w.ctr, nruns, s.n1, s.chunk_unit, s.chunk_slices, s.chunk_target, w.run_nch);
     // exclusive scan in place; the tile sums buffer of the dense scan is free again
     e = scan_generic<uint32_t, false>(w.run_nch, w.run_nch, nruns + 1, w.tsum32, w.ctr + C_NCHUNKS, st);
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL(k_make_chunks, dim3((nruns + 255) / 256), dim3(256), 0, st, (const uint32_t*)w.dense_base,
-                     (const uint32_t*)w.run_nch, (const int32_t*)w.ctr, nruns, s.n1, s.chunk_slices, w.chunks);
+  hipLaunchKernelGGL(k_make_chunks, dim3(grid_for(w.nch_max, 256, 1024)), dim3(256), 0, st,
+                     (const uint32_t*)w.dense_base, (const uint32_t*)w.run_nch, (const int32_t*)w.ctr, nruns, s.n1,
+                     s.chunk_unit, s.chunk_slices, s.chunk_target, w.chunks);
   return hipGetLastError();
 }
 

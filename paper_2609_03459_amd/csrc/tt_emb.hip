@@ -72,7 +72,6 @@ static size_t layout(const Shape& s, int64_t M, int64_t B, char* base, Work* w, 
   W->uniq_i3 = (int32_t*)take(4 * m);
   W->occ_start = (int32_t*)take(4 * (m + 1));
   W->pg_start = (int32_t*)take(4 * (m + 1));
-  W->pg_key = (uint32_t*)take(4 * m);
   W->dense_cnt = (uint32_t*)take(4 * s.ndense);
   W->dense_base = (uint32_t*)take(4 * s.ndense);
   W->dense_pg = (int32_t*)take(4 * s.ndense);
@@ -84,15 +83,18 @@ static size_t layout(const Shape& s, int64_t M, int64_t B, char* base, Work* w, 
   int64_t nsl_max = m / s.slice_rows + groups_max + 1;
   if (s.dedup && s.ndense * per_prefix < nsl_max) nsl_max = s.ndense * per_prefix;
   if (nsl_max > m) nsl_max = m;
-  // chunks: ceil(slices of run / chunk_slices) per non-empty (t, i2) run, or with
+  // chunks: ceil(slices of run / chunk_len) per non-empty (t, i2) run, where chunk_len is
+  // below chunk_slices only while that gives fewer than 2 chunk_target chunks; or with
   // SCHED_GROUP ceil(slices of group / GROUP_CHUNK_MAX) per prefix group
+  int64_t full = nsl_max / s.chunk_slices, fine = nsl_max / s.chunk_unit;
+  if (fine > 2 * (int64_t)s.chunk_target) fine = 2 * (int64_t)s.chunk_target;
+  if (full < fine) full = fine;
   int64_t nch_max = s.sched == SCHED_GROUP ? groups_max + nsl_max / GROUP_CHUNK_MAX + 1
-                                           : nsl_max / s.chunk_slices + (int64_t)s.T * s.n2 + 1;
+                                           : full + (int64_t)s.T * s.n2 + 1;
   if (nch_max > nsl_max) nch_max = nsl_max;
   W->nsl_max = nsl_max;
   W->nch_max = nch_max;
   W->slices = (int4*)take(16 * nsl_max);
-  W->slice_i1 = (int32_t*)take(4 * nsl_max);
   W->run_nch = (uint32_t*)take(4 * ((int64_t)s.T * s.n2 + 1));
   W->chunks = (int4*)take(16 * nch_max);
   W->E = (float*)take(4 * (size_t)m * s.D);
@@ -130,6 +132,10 @@ static size_t layout(const Shape& s, int64_t M, int64_t B, char* base, Work* w, 
   const int par = sort_passes(s.key_bits) & 1;
   W->sorted_keys = W->keys[par];
   W->sorted_pos = W->vals[par];
+  // the other halves of the sort's ping-pong buffers are free once it is done, and at most
+  // m prefix groups and nsl_max <= m slices follow
+  W->pg_key = W->keys[par ^ 1];
+  W->slice_i1 = reinterpret_cast<int32_t*>(W->vals[par ^ 1]);
   W->M = M;
   W->B = B;
   return off;
@@ -173,12 +179,24 @@ static int prefix_slice_rows(const Shape& s) {
   return s.R == 64 && s.d1 == 4 && s.d2 == 4 && s.d3 == 8 ? 16 : SLICE_ROWS;
 }
 
-// Slices per chunk: 32 where the matrix-core kernels of R = 32 keep B in registers over a
-// chunk (TTEMB_CHUNK), one quad on the R = 64 shape, four for the kernels of any shape,
-// which keep nothing between stacks.
-static int view_chunk_slices(const Shape& s) {
-  const bool d44 = s.d1 == 4 && s.d2 == 4;
-  return s.R == 32 && d44 && (s.d3 == 8 || s.d3 == 2) ? TTEMB_CHUNK : TTEMB_R64_CHUNK;
+// Fewest and most slices per chunk (chunk_len, common.h, has the reasons).  A one-slice
+// stack (d1 >= 16) is taken two at a time, which keeps the chunk list within what the shared
+// buffers above save.
+static void view_chunk_slices(Shape* s) {
+  const bool d44 = s->d1 == 4 && s->d2 == 4;
+  if (s->R == 64 && d44 && s->d3 == 8) {
+    s->chunk_unit = s->chunk_slices = R64_CHUNK;
+    s->chunk_target = 1;
+  } else if (s->R == 32 && d44 && (s->d3 == 8 || s->d3 == 2)) {
+    s->chunk_unit = QUAD;
+    s->chunk_slices = R32_CHUNK;
+    s->chunk_target = R32_CHUNK_TARGET;
+  } else {
+    const int sq = any_stack_slices(*s);
+    s->chunk_unit = sq < 2 ? 2 : sq;
+    s->chunk_slices = ANY_CHUNK_STACKS * s->chunk_unit;
+    s->chunk_target = ANY_CHUNK_TARGET;
+  }
 }
 
 static int bit_length(uint64_t x) {
@@ -241,7 +259,7 @@ static tt_emb_status create_view(const tt_emb_desc* d, int L, const int32_t* nk,
   s.slice_rows = prefix_slice_rows(s);
   s.dedup = 1;
   s.sched = SCHED_STEAL;
-  s.chunk_slices = view_chunk_slices(s);
+  view_chunk_slices(&s);
   s.L = L;
   for (int k = 0; k < MAX_CORES; ++k) {
     s.nk[k] = k < L ? nk[k] : 1;
@@ -657,9 +675,9 @@ tt_emb_status tt_emb_debug_grouping(tt_emb_handle h, void* workspace, int64_t* u
     delete[] tmp;
   }
   if (uniq_digits && U > 0) {
-    // decoded on the device by the kernels' own key decoder, one digit at a time,
-    // into the radix buffer that the sort no longer needs
-    int32_t* scratch = reinterpret_cast<int32_t*>(w.sorted_keys == w.keys[0] ? w.keys[1] : w.keys[0]);
+    // decoded on the device by the kernels' own key decoder, one digit at a time, into
+    // the row buffer (no row of E outlives the call that made it)
+    int32_t* scratch = reinterpret_cast<int32_t*>(w.E);
     int32_t* tmp = new (std::nothrow) int32_t[U];
     if (!tmp) return TT_EMB_ENOMEM;
     for (int k = 0; k < 3 && ok; ++k) {

@@ -87,3 +87,15 @@ def test_two_cores(lib, orc, n, d, R):
     ref, mag = orc.backward_n(case)[0], orc.backward_n(mag_case)[0]
     for k in range(2):
         assert_close(f"dG{k + 1} {n} {d}", grads[k].cpu().numpy(), ref[k], mag[k])
+
+
+@pytest.mark.parametrize("d,R", [((4, 4, 8), 32), ((4, 4, 2), 32), ((4, 4, 4), 16)])
+@pytest.mark.parametrize("n1", [5, 330])
+def test_chunk_lengths(lib, orc, d, R, n1):
+    # slices per chunk follow the slice count: about 1,200 slices (shortest chunks) and, with one
+    # single-row group per prefix, 66,000 (8-slice chunks at R = 32, four stacks at R = 16), in runs
+    # whose last chunk is short
+    case = ttgen.tiny(8400 + n1, 1, (n1, 240 if n1 == 5 else 200, 3), d, R, B=4000 if n1 == 5 else 120000, single=True,
+                      sigma=0.3)
+    emb = _check(lib, orc, case, f"chunks n1={n1} {d} R={R}")
+    assert emb.counts()["nslices"] > (1000 if n1 == 5 else 40000)
