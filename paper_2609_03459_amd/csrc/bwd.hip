@@ -25,7 +25,7 @@ hipError_t launch_bwd_r32(const Shape& s, const Work& w, const float* G1, const 
 // ---------------------------------------------------------------------------
 // What chunk c = [i0, i1) of the sorted occurrences sums.  A row's occurrences
 // are contiguous, so only the chunk's first row can have begun before it and only
-// its last row can go on after it.  A row of at most SEG_CHUNK occurrences that
+// its last row can go on after it.  A row of at most one chunk's occurrences that
 // crosses the chunk end is summed whole by the chunk of its first occurrence,
 // which reads on past its end (less than one chunk), and skipped by the next
 // chunk.  A longer row is split: each chunk sums its part into a partial (head:
@@ -36,7 +36,8 @@ struct SegEnds {
   int u_head, u_tail;    // the rows whose sums go to the head / tail partial, else -1
 };
 __device__ __forceinline__ SegEnds seg_ends(const int32_t* __restrict__ sorted_uid,
-                                            const int32_t* __restrict__ occ_start, int i0, int i1, int nvalid) {
+                                            const int32_t* __restrict__ occ_start, int i0, int i1, int nvalid,
+                                            int lg) {
   SegEnds e;
   e.ib = i0;
   e.ie = i1;
@@ -44,7 +45,7 @@ __device__ __forceinline__ SegEnds seg_ends(const int32_t* __restrict__ sorted_u
   const int uf = sorted_uid[i0];
   if (i0 > 0 && sorted_uid[i0 - 1] == uf) {
     const int end = occ_start[uf + 1];
-    if (end - occ_start[uf] <= SEG_CHUNK)
+    if (end - occ_start[uf] <= 1 << lg)
       e.ib = end;  // summed by the previous chunk
     else
       e.u_head = uf;
@@ -52,7 +53,7 @@ __device__ __forceinline__ SegEnds seg_ends(const int32_t* __restrict__ sorted_u
   const int ul = sorted_uid[i1 - 1];
   if (i1 < nvalid && sorted_uid[i1] == ul) {
     const int end = occ_start[ul + 1];
-    if (end - occ_start[ul] <= SEG_CHUNK)
+    if (end - occ_start[ul] <= 1 << lg)
       e.ie = end;  // read on to the row's end
     else if (ul != e.u_head)
       e.u_tail = ul;
@@ -97,7 +98,7 @@ __global__ void __launch_bounds__(256) k_sorted_bag(const uint32_t* __restrict__
     if (i0 + 256 * k < nvalid) sorted_bag[i0 + 256 * k] = b[k];
 }
 
-// One wave per chunk of SEG_CHUNK sorted occurrences; lanes hold 4 columns
+// D not a multiple of 4: one wave per chunk of sorted occurrences; lanes hold 4 columns
 // each (column blocks of 256); occurrence indices are fetched 64 at a time and
 // the grad_out rows of 8 occurrences are loaded before they are summed.
 // Four waves per workgroup (one-wave workgroups would cap the waves a CU holds),
@@ -108,13 +109,14 @@ __global__ void __launch_bounds__(64 * SEG_WAVES) k_seg_dE(const float* __restri
                                                const int32_t* __restrict__ sorted_bag,
                                                const int32_t* __restrict__ occ_start,
                                                const int32_t* __restrict__ ctr, int D, float* __restrict__ dE,
-                                               float* __restrict__ part) {
+                                               float* __restrict__ part, int lg) {
   const int nvalid = ctr[C_NVALID];
   const int c = blockIdx.x * SEG_WAVES + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int i0 = c * SEG_CHUNK;
+  const int i0 = c << lg;
   if (i0 >= nvalid) return;
   const int lane = lane_id();
-  const SegEnds ends = seg_ends(sorted_uid, occ_start, i0, i0 + SEG_CHUNK < nvalid ? i0 + SEG_CHUNK : nvalid, nvalid);
+  const int i1 = i0 + (1 << lg) < nvalid ? i0 + (1 << lg) : nvalid;
+  const SegEnds ends = seg_ends(sorted_uid, occ_start, i0, i1, nvalid, lg);
   const int ib = ends.ib, ie = ends.ie;
   if (ib >= ie) return;
   for (int j0 = 0; j0 < D; j0 += 256) {
@@ -158,32 +160,29 @@ __global__ void __launch_bounds__(64 * SEG_WAVES) k_seg_dE(const float* __restri
   }
 }
 
-// D = 128 and D = 32: a lane owns two columns (one 8-byte load per occurrence;
-// for D = 32 sixteen lanes cover a row and the other lanes repeat their loads),
-// the bag index of each occurrence is read into a scalar register so every dV row
-// is a uniform base, and 16 (D = 128) or 32 (D = 32) rows are in flight before
-// they are summed in order.  Chunks go in sorted order, an eighth of them per XCD,
-// so each XCD reads the grad_out rows and bag ids of about one table, and more of
-// them hit its L2.
-template <int D>
-__device__ __forceinline__ void seg_rows(const float* __restrict__ dV, const int32_t* __restrict__ sorted_uid,
-                                         const int32_t* __restrict__ sorted_bag, const int32_t* __restrict__ occ_start,
-                                         const int32_t* __restrict__ ctr, float* __restrict__ dE,
-                                         float* __restrict__ part) {
-  constexpr int LN = D / 2;               // lanes that own columns
-  constexpr int KB = D == 128 ? 16 : 32;  // rows in flight
+// D = 128: a lane owns two columns (one 8-byte load per occurrence), the bag index of each
+// occurrence is read into a scalar register so every dV row is a uniform base, and 16 rows
+// are in flight before they are summed in order.  Chunks go in sorted order, an eighth of
+// them per XCD, so each XCD reads the grad_out rows and bag ids of about one table, and
+// more of them hit its L2.
+__global__ void __launch_bounds__(64 * SEG_WAVES) k_seg_dE128(const float* __restrict__ dV, const int32_t* __restrict__ sorted_uid,
+                                                  const int32_t* __restrict__ sorted_bag,
+                                                  const int32_t* __restrict__ occ_start,
+                                                  const int32_t* __restrict__ ctr, float* __restrict__ dE,
+                                                  float* __restrict__ part, int lg) {
+  constexpr int D = 128, KB = 16;  // KB rows in flight
   const int nvalid = ctr[C_NVALID];
   const int c = (int)xcd_block(blockIdx.x, gridDim.x) * SEG_WAVES + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int i0 = c * SEG_CHUNK;
+  const int64_t i0 = (int64_t)c << lg;
   if (i0 >= nvalid) return;  // also the blocks past the chunk count that round the grid to 8
   const int lane = lane_id();
-  const int col = lane % LN;
-  const SegEnds ends = seg_ends(sorted_uid, occ_start, i0, i0 + SEG_CHUNK < nvalid ? i0 + SEG_CHUNK : nvalid, nvalid);
+  const int64_t i1 = i0 + (1 << lg) < nvalid ? i0 + (1 << lg) : nvalid;
+  const SegEnds ends = seg_ends(sorted_uid, occ_start, (int)i0, (int)i1, nvalid, lg);
   const int ib = ends.ib, ie = ends.ie;
   if (ib >= ie) return;
   // dE of all unique rows beyond the last-level cache: stored non-temporally.  The row
-  // goes through a descriptor of its 4 D bytes (lanes past LN fall outside it), so the
-  // two cache policies stay two distinct stores
+  // goes through a descriptor of its 4 D bytes, so the two cache policies stay two
+  // distinct stores
   const bool de_nt = (uint64_t)(uint32_t)ctr[C_U] * (4u * D) > STREAM_BYTES;
   auto flush = [&](int u, float2 acc) {
     typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
@@ -207,7 +206,7 @@ __device__ __forceinline__ void seg_rows(const float* __restrict__ dV, const int
       for (int kk = 0; kk < KB; ++kk) {
         const int k = k0 + kk < cnt ? k0 + kk : k0;  // clamped: every load is unconditional
         const int b = __builtin_amdgcn_readlane(my_b, k);
-        v[kk] = reinterpret_cast<const float2*>(dV + (size_t)b * D)[col];
+        v[kk] = reinterpret_cast<const float2*>(dV + (size_t)b * D)[lane];
       }
 #pragma unroll
       for (int kk = 0; kk < KB; ++kk) {
@@ -226,22 +225,102 @@ __device__ __forceinline__ void seg_rows(const float* __restrict__ dV, const int
   }
   flush(cur, acc);
 }
-__global__ void __launch_bounds__(64 * SEG_WAVES) k_seg_dE128(const float* __restrict__ dV, const int32_t* __restrict__ sorted_uid,
-                                                  const int32_t* __restrict__ sorted_bag,
-                                                  const int32_t* __restrict__ occ_start,
-                                                  const int32_t* __restrict__ ctr, float* __restrict__ dE,
-                                                  float* __restrict__ part) {
-  seg_rows<128>(dV, sorted_uid, sorted_bag, occ_start, ctr, dE, part);
-}
-__global__ void __launch_bounds__(64 * SEG_WAVES) k_seg_dE32(const float* __restrict__ dV, const int32_t* __restrict__ sorted_uid,
-                                                 const int32_t* __restrict__ sorted_bag,
-                                                 const int32_t* __restrict__ occ_start,
-                                                 const int32_t* __restrict__ ctr, float* __restrict__ dE,
-                                                 float* __restrict__ part) {
-  seg_rows<32>(dV, sorted_uid, sorted_bag, occ_start, ctr, dE, part);
+
+// Any other D that is a multiple of 4: LPR lanes share a chunk and a lane owns four columns
+// (and every LPR-th four after them when D > 4 LPR), so a wave walks 64 / LPR chunks at once
+// and one load instruction takes that many rows.  SEGV_NOTE
+// Row ids and bags come in 16-byte loads from the chunk's aligned start (the occurrences
+// before ib are skipped), SEG_KB rows are in flight per chunk, and the chunks go in sorted
+// order, an eighth of them per XCD.
+constexpr int SEG_KB = 8;
+template <int LPR>
+__global__ void __launch_bounds__(64 * SEG_WAVES) k_seg_vec(const float4* __restrict__ dV, const int32_t* __restrict__ sorted_uid,
+                                                const int32_t* __restrict__ sorted_bag,
+                                                const int32_t* __restrict__ occ_start,
+                                                const int32_t* __restrict__ ctr, int D4, float* __restrict__ dE,
+                                                float* __restrict__ part, int lg) {
+  const int nvalid = ctr[C_NVALID];
+  const int c = (int)xcd_block(blockIdx.x, gridDim.x) * (64 * SEG_WAVES / LPR) + (int)threadIdx.x / LPR;
+  const int64_t i0 = (int64_t)c << lg;
+  if (i0 >= nvalid) return;
+  const int sub = threadIdx.x % LPR;
+  const int64_t i1 = i0 + (1 << lg) < nvalid ? i0 + (1 << lg) : nvalid;
+  const SegEnds ends = seg_ends(sorted_uid, occ_start, (int)i0, (int)i1, nvalid, lg);
+  const int ib = ends.ib, ie = ends.ie;
+  if (ib >= ie) return;
+  for (int j = sub; j < D4; j += LPR) {
+    int cur = sorted_uid[ib];
+    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int base = ib & ~(SEG_KB - 1); base < ie; base += SEG_KB) {
+      int u[SEG_KB], b[SEG_KB];
+      if (base + SEG_KB <= nvalid) {
+#pragma unroll
+        for (int q = 0; q < SEG_KB / 4; ++q) {
+          const int4 uq = reinterpret_cast<const int4*>(sorted_uid + base)[q];
+          const int4 bq = reinterpret_cast<const int4*>(sorted_bag + base)[q];
+          u[4 * q] = uq.x;
+          u[4 * q + 1] = uq.y;
+          u[4 * q + 2] = uq.z;
+          u[4 * q + 3] = uq.w;
+          b[4 * q] = bq.x;
+          b[4 * q + 1] = bq.y;
+          b[4 * q + 2] = bq.z;
+          b[4 * q + 3] = bq.w;
+        }
+      } else {
+#pragma unroll
+        for (int k = 0; k < SEG_KB; ++k) {
+          const int i = base + k < nvalid ? base + k : nvalid - 1;
+          u[k] = sorted_uid[i];
+          b[k] = sorted_bag[i];
+        }
+      }
+      float4 v[SEG_KB];
+#pragma unroll
+      for (int k = 0; k < SEG_KB; ++k) v[k] = dV[(size_t)b[k] * D4 + j];
+#pragma unroll
+      for (int k = 0; k < SEG_KB; ++k) {
+        if (base + k < ib || base + k >= ie) continue;
+        if (u[k] != cur) {
+          reinterpret_cast<float4*>(seg_dst(ends, cur, c, 4 * D4, dE, part))[j] = acc;
+          cur = u[k];
+          acc = make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+        acc.x += v[k].x;
+        acc.y += v[k].y;
+        acc.z += v[k].z;
+        acc.w += v[k].w;
+      }
+    }
+    reinterpret_cast<float4*>(seg_dst(ends, cur, c, 4 * D4, dE, part))[j] = acc;
+  }
 }
 
-// Rows of more than SEG_CHUNK occurrences: chunk c0 + 1, where c0 holds the
+// Lanes per row of a D = 4 D4 columns kernel
+static int seg_lanes(int D) {
+  int lpr = 1;
+  while (4 * lpr < D && lpr < 64) lpr *= 2;
+  return lpr;
+}
+// Chunks a wave walks at once
+static int seg_per_wave(const Shape& s) { return s.D == 128 || s.D % 4 ? 1 : 64 / seg_lanes(s.D); }
+
+// The longest chunk (256 occurrences) that still gives SEG_WAVES_WANTED waves, at least 32: a
+// wave sums its chunk one occurrence after the other, SEGC_NOTE
+constexpr int64_t SEG_WAVES_WANTED = 8192;
+int seg_log2(const Shape& s, int64_t M) {
+  int lg = SEG_MAX_LOG2;
+  while (lg > SEG_MIN_LOG2 && (M >> lg) < SEG_WAVES_WANTED * seg_per_wave(s)) --lg;
+  return lg;
+}
+int64_t seg_chunks_max(const Shape& s, int64_t M) {
+  // a chunk shorter than 256 is taken only while twice its length gives too few waves
+  const int64_t fine = (M + (1 << SEG_MIN_LOG2) - 1) >> SEG_MIN_LOG2, full = (M + (1 << SEG_MAX_LOG2) - 1) >> SEG_MAX_LOG2;
+  const int64_t few = 2 * SEG_WAVES_WANTED * seg_per_wave(s) + 2;
+  return fine < few ? fine : (few > full ? few : full);
+}
+
+// Rows of more than one chunk's occurrences: chunk c0 + 1, where c0 holds the
 // row's first occurrence, finishes the row from c0's tail partial and the head
 // partials of every following chunk, in chunk order.  A block screens 64 chunks
 // with one lane each (few of them start inside such a row).  Rows of at most
@@ -253,17 +332,18 @@ constexpr int FIX_SCREEN = 64;  // chunks screened per block
 constexpr int FIX_WAVES = 16;
 constexpr int FIX_SMALL = 16;
 __device__ __forceinline__ int fix_row(const int32_t* __restrict__ sorted_uid, const int32_t* __restrict__ occ_start,
-                                       int c, int* c0, int* c1) {
-  const int u = sorted_uid[c * SEG_CHUNK];
+                                       int c, int lg, int* c0, int* c1) {
+  const int u = sorted_uid[(int64_t)c << lg];
   const int lo = occ_start[u], hi = occ_start[u + 1];
-  *c0 = lo / SEG_CHUNK;
-  *c1 = (hi - 1) / SEG_CHUNK;
+  *c0 = lo >> lg;
+  *c1 = (hi - 1) >> lg;
   return u;
 }
 __global__ void __launch_bounds__(64 * FIX_WAVES) k_seg_fix(const int32_t* __restrict__ sorted_uid,
                                                             const int32_t* __restrict__ occ_start,
                                                             const int32_t* __restrict__ ctr, int D,
-                                                            const float* __restrict__ part, float* __restrict__ dE) {
+                                                            const float* __restrict__ part, float* __restrict__ dE,
+                                                            int lg) {
   __shared__ float red[FIX_WAVES][256];
   __shared__ uint64_t flagged[2];  // rows with few / many head partials
   const int nvalid = ctr[C_NVALID];
@@ -271,11 +351,11 @@ __global__ void __launch_bounds__(64 * FIX_WAVES) k_seg_fix(const int32_t* __res
   if (w == 0) {
     const int c = blockIdx.x * FIX_SCREEN + lane;
     bool fix = false, big = false;
-    if (c > 0 && (int64_t)c * SEG_CHUNK < nvalid) {
-      const int u = sorted_uid[c * SEG_CHUNK];
+    if (c > 0 && (int64_t)c << lg < nvalid) {
+      const int u = sorted_uid[(int64_t)c << lg];
       const int lo = occ_start[u], hi = occ_start[u + 1];
-      fix = lo / SEG_CHUNK == c - 1 && hi - lo > SEG_CHUNK;
-      big = (hi - 1) / SEG_CHUNK - lo / SEG_CHUNK > FIX_SMALL;
+      fix = lo >> lg == c - 1 && hi - lo > 1 << lg;
+      big = ((hi - 1) >> lg) - (lo >> lg) > FIX_SMALL;
     }
     const uint64_t m_small = __ballot(fix && !big), m_big = __ballot(fix && big);
     if (lane == 0) {
@@ -290,7 +370,7 @@ __global__ void __launch_bounds__(64 * FIX_WAVES) k_seg_fix(const int32_t* __res
     for (int v = 0; m; ++v, m &= m - 1) {
       if (v % FIX_WAVES != w) continue;
       int c0, c1;
-      const int u = fix_row(sorted_uid, occ_start, blockIdx.x * FIX_SCREEN + __builtin_ctzll(m), &c0, &c1);
+      const int u = fix_row(sorted_uid, occ_start, blockIdx.x * FIX_SCREEN + __builtin_ctzll(m), lg, &c0, &c1);
       for (int j = lane; j < D; j += 64) {
         float a[4] = {part[((int64_t)c0 * 2 + 1) * D + j], 0.f, 0.f, 0.f};
         int k = c0 + 1;
@@ -308,7 +388,7 @@ __global__ void __launch_bounds__(64 * FIX_WAVES) k_seg_fix(const int32_t* __res
     const int c = blockIdx.x * FIX_SCREEN + __builtin_ctzll(m);
     m &= m - 1;
     int c0, c1;
-    const int u = fix_row(sorted_uid, occ_start, c, &c0, &c1);
+    const int u = fix_row(sorted_uid, occ_start, c, lg, &c0, &c1);
     const int n = c1 - c0;  // head partials of chunks c0+1 .. c1
     const int k_lo = c0 + 1 + (int)(((int64_t)n * w) / FIX_WAVES);
     const int k_hi = c0 + 1 + (int)(((int64_t)n * (w + 1)) / FIX_WAVES);
@@ -778,23 +858,38 @@ hipError_t launch_backward(const Shape& s, const Work& w, const float* G1, const
     return fill_f32(dG3, n3s, 0.f, st);
   }
   float* dE = w.E;
-  const int nseg = (int)((M + SEG_CHUNK - 1) / SEG_CHUNK);
+  const int lg = seg_log2(s, M);
+  const int nseg = (int)((M + (1 << lg) - 1) >> lg);
   hipLaunchKernelGGL(k_sorted_bag, dim3(xcd_grid((unsigned)((M + SB_ITEMS * 256 - 1) / (SB_ITEMS * 256)))), dim3(256),
                      0, st, (const uint32_t*)w.sorted_pos, (const int32_t*)w.bag_of, (const int32_t*)w.ctr,
                      w.sorted_bag);
   prof_begin(prof, K_SEG_SUM, st);
-  if (s.D == 128 || s.D == 32) {
-    hipLaunchKernelGGL(s.D == 128 ? k_seg_dE128 : k_seg_dE32, dim3(xcd_grid((nseg + SEG_WAVES - 1) / SEG_WAVES)),
-                       dim3(64 * SEG_WAVES), 0, st, dV, (const int32_t*)w.sorted_uid, (const int32_t*)w.sorted_bag,
-                       (const int32_t*)w.occ_start, (const int32_t*)w.ctr, dE, w.seg_part);
+  if (s.D == 128) {
+    hipLaunchKernelGGL(k_seg_dE128, dim3(xcd_grid((nseg + SEG_WAVES - 1) / SEG_WAVES)), dim3(64 * SEG_WAVES), 0, st, dV,
+                       (const int32_t*)w.sorted_uid, (const int32_t*)w.sorted_bag, (const int32_t*)w.occ_start,
+                       (const int32_t*)w.ctr, dE, w.seg_part, lg);
+  } else if (s.D % 4 == 0) {
+    const int lpr = seg_lanes(s.D), per = 64 * SEG_WAVES / lpr;
+    auto fn = k_seg_vec<64>;
+    switch (lpr) {
+      case 1: fn = k_seg_vec<1>; break;
+      case 2: fn = k_seg_vec<2>; break;
+      case 4: fn = k_seg_vec<4>; break;
+      case 8: fn = k_seg_vec<8>; break;
+      case 16: fn = k_seg_vec<16>; break;
+      case 32: fn = k_seg_vec<32>; break;
+    }
+    hipLaunchKernelGGL(fn, dim3(xcd_grid((nseg + per - 1) / per)), dim3(64 * SEG_WAVES), 0, st,
+                       reinterpret_cast<const float4*>(dV), (const int32_t*)w.sorted_uid, (const int32_t*)w.sorted_bag,
+                       (const int32_t*)w.occ_start, (const int32_t*)w.ctr, s.D / 4, dE, w.seg_part, lg);
   } else {
     hipLaunchKernelGGL(k_seg_dE, dim3((nseg + SEG_WAVES - 1) / SEG_WAVES), dim3(64 * SEG_WAVES), 0, st, dV, (const int32_t*)w.sorted_uid,
                        (const int32_t*)w.sorted_bag, (const int32_t*)w.occ_start,
-                       (const int32_t*)w.ctr, s.D, dE, w.seg_part);
+                       (const int32_t*)w.ctr, s.D, dE, w.seg_part, lg);
   }
   prof_end(prof, K_SEG_SUM, st);
   hipLaunchKernelGGL(k_seg_fix, dim3((nseg + FIX_SCREEN - 1) / FIX_SCREEN), dim3(64 * FIX_WAVES), 0, st, (const int32_t*)w.sorted_uid, (const int32_t*)w.occ_start,
-                     (const int32_t*)w.ctr, s.D, (const float*)w.seg_part, dE);
+                     (const int32_t*)w.ctr, s.D, (const float*)w.seg_part, dE, lg);
   if (fast) return launch_bwd_r32(s, w, G1, G2, G3, dG1, dG2, dG3, lr, update, prof, st);
   if (!w.dDpart || !w.g3lo) return hipErrorInvalidValue;
   if (bwd_r64_supported(s, w.M)) {  // MFMA partials, then the same segment sums (dG2 by a product)

@@ -86,7 +86,8 @@ __host__ __device__ __forceinline__ uint32_t chunk_len(uint32_t nslices, int uni
   while (cs > (uint32_t)unit && nslices / cs < (uint32_t)target) cs >>= 1;
   return cs;
 }
-constexpr int SEG_CHUNK = 256;   // sorted occurrences per dE chunk
+// Sorted occurrences per chunk of the dE sums: SEG_MAX, fewer on smaller calls (seg_log2).
+constexpr int SEG_MIN_LOG2 = 5, SEG_MAX_LOG2 = 8;
 constexpr int MAX_BWD_WG = 256;  // workgroups of the MFMA backward (one per CU on MI355X)
 
 // Device pointers carved out of the caller's workspace.
@@ -137,7 +138,7 @@ struct Work {
   int32_t* ckpt_tag;      // [CKPT_SLOTS] prefix group held by each entry, -1 = none
   int64_t nsl_max, nch_max;
   float* E;               // [M][D]: E rows (forward), dE rows (backward)
-  float* seg_part;        // [nseg][2][D] partial dE of rows that cross a chunk
+  float* seg_part;        // [seg_chunks_max][2][D] partial dE of rows that cross a chunk
   uint32_t* sorted_keys;  // = keys[x] after the sort
   uint32_t* sorted_pos;   // = vals[x] after the sort
   int64_t M;              // capacity in occurrences
@@ -192,6 +193,10 @@ int64_t chain_level_floats(const Shape& s);
 int64_t split_partial_floats(const Shape& s);
 // G -= lr * dG on n floats.
 hipError_t launch_sgd1(float* G, const float* dG, int64_t n, float lr, hipStream_t st);
+// Chunks of the dE segment sums: log2 of the occurrences per chunk of a call, and the most
+// chunks of any call of up to M occurrences.
+int seg_log2(const Shape& s, int64_t M);
+int64_t seg_chunks_max(const Shape& s, int64_t M);
 // Whether the MFMA backward (and its partial-sum workspace) serves this shape.
 bool bwd_r32_supported(const Shape& s, int64_t max_indices);
 // Whether the MFMA backward for R = 64 serves this shape (it writes the generic

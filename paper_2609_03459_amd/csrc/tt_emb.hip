@@ -45,7 +45,6 @@ static size_t layout(const Shape& s, int64_t M, int64_t B, char* base, Work* w, 
   const int64_t sort_tiles = (m + SORT_TILE - 1) / SORT_TILE;
   const int64_t scan_tiles = (m + SCAN_TILE - 1) / SCAN_TILE;
   const int64_t dscan_tiles = (s.ndense + SCAN_TILE - 1) / SCAN_TILE;
-  const int64_t nseg = (m + SEG_CHUNK - 1) / SEG_CHUNK;
   size_t off = 0;
   auto take = [&](size_t bytes) -> char* {
     char* p = base ? base + off : nullptr;
@@ -110,7 +109,7 @@ static size_t layout(const Shape& s, int64_t M, int64_t B, char* base, Work* w, 
   W->ckpt_tag = generic ? (int32_t*)take(4 * CKPT_SLOTS) : nullptr;
   if (fwd_end) *fwd_end = off;
   // --- regions of the backward only ---
-  W->seg_part = (float*)take(4 * (size_t)nseg * 2 * s.D);
+  W->seg_part = (float*)take(4 * (size_t)seg_chunks_max(s, m) * 2 * s.D);
   W->sorted_bag = (int32_t*)take(4 * m);
   // gradient partials: the R = 32 MFMA backward's rank halves, or the other backwards'
   // per-slice dA and dC and per-row dD with the (t, i3) order of the rows
