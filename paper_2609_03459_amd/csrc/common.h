@@ -56,9 +56,7 @@ enum : int {
 enum : int { ERR_INDEX = 1, ERR_OFFSETS = 2 };
 
 // Fixed tiling constants.
-constexpr int SORT_THREADS = 256;
-constexpr int SORT_ITEMS = 16;
-constexpr int SORT_TILE = SORT_THREADS * SORT_ITEMS;  // keys per radix tile
+constexpr int SORT_TILE = 4096;  // keys per radix tile
 constexpr int RADIX_MAX_BITS = 11;               // widest radix digit
 constexpr int RADIX_MAX = 1 << RADIX_MAX_BITS;
 // LSD radix passes for keys of key_bits bits: equal-width digits of at most RADIX_MAX_BITS
@@ -256,6 +254,28 @@ __device__ __forceinline__ T wave_incl_scan(T v) {
     if (lane >= o) v += u;
   }
   return v;
+}
+
+// Exact quotients of 32-bit values by a divisor known on the host, without a division:
+// x / d = (((x - h) >> 1) + h) >> shift with h = mulhi(x, mul) for d >= 2 (Granlund and
+// Montgomery, "Division by invariant integers using multiplication", 1994); mul = 0 marks
+// d = 1.
+struct FastDiv {
+  uint32_t d, mul, shift;
+};
+inline FastDiv fast_div_of(uint32_t d) {
+  FastDiv f = {d, 0, 0};
+  if (d < 2) return f;
+  int l = 0;
+  while (l < 32 && (1ull << l) < d) ++l;  // ceil(log2 d)
+  f.mul = (uint32_t)((((1ull << l) - d) << 32) / d + 1);
+  f.shift = (uint32_t)(l - 1);
+  return f;
+}
+__host__ __device__ __forceinline__ uint32_t quot(uint32_t x, FastDiv f) {
+  if (!f.mul) return x;
+  const uint32_t h = (uint32_t)(((uint64_t)x * f.mul) >> 32);
+  return (((x - h) >> 1) + h) >> f.shift;
 }
 
 // Exclusive scan over a block of NT threads; smem holds NT/64 values.

@@ -37,9 +37,11 @@ hipError_t fill_f32(float* p, int64_t n, float v, hipStream_t st) {
 }
 
 // ---------------------------------------------------------------------------
-// ingest: keys, positions and bag ids, one tile of SORT_TILE occurrences per block
+// ingest: keys and bag ids, one tile of SORT_TILE occurrences per block
 // ---------------------------------------------------------------------------
-constexpr int INGEST_WIN = SORT_TILE + 1;
+constexpr int INGEST_THREADS = 512;
+constexpr int INGEST_ITEMS = SORT_TILE / INGEST_THREADS;
+constexpr int INGEST_WIN = 4 * SORT_TILE;  // most bags of a tile whose starts are marked in LDS
 
 __device__ __forceinline__ int64_t upper_bound_global(const int64_t* a, int64_t lo, int64_t hi, int64_t x) {
   // first index in [lo, hi) with a[i] > x (hi if none)
@@ -68,69 +70,93 @@ __global__ void k_tile_bags(const int64_t* __restrict__ offsets, int64_t NB, int
   for (int64_t k = (lo + SORT_TILE - 1) / SORT_TILE; k * SORT_TILE < hi; ++k) tile_bag[k] = (int32_t)b;
 }
 
-__global__ void __launch_bounds__(SORT_THREADS) k_ingest(const int64_t* __restrict__ idx, int64_t M,
-                                                         const int64_t* __restrict__ offsets,
-                                                         const int32_t* __restrict__ tile_bag, int64_t B, int T,
-                                                         int64_t N, uint32_t Npad, uint32_t kinv,
-                                                         uint32_t* __restrict__ keys, uint32_t* __restrict__ vals,
-                                                         int32_t* __restrict__ bag_of, int32_t* __restrict__ ctr,
-                                                         uint32_t* __restrict__ counts0, int nb0, int ntiles) {
-  __shared__ int64_t win[INGEST_WIN];
+// The bag of an occurrence: every bag of the tile marks its first occurrence in LDS with its
+// number (of several that begin there, empty ones among them, the last one counts), and a
+// running maximum over the tile carries the numbers on.  (A binary search per occurrence
+// over the bags' starts in LDS, before, was a chain of a dozen LDS reads for each of a
+// thread's 16: 46 us with the tile-to-bag map for 5.2M occurrences, now 30; 22 -> 13 for 15k.)
+__global__ void __launch_bounds__(INGEST_THREADS) k_ingest(const int64_t* __restrict__ idx, int64_t M,
+                                                           const int64_t* __restrict__ offsets,
+                                                           const int32_t* __restrict__ tile_bag, int64_t B, int T,
+                                                           int64_t N, uint32_t Npad, uint32_t kinv, FastDiv divB,
+                                                           uint32_t* __restrict__ keys, int32_t* __restrict__ bag_of,
+                                                           int32_t* __restrict__ ctr, uint32_t* __restrict__ counts0,
+                                                           int nb0, int ntiles) {
+  __shared__ int32_t mark[SORT_TILE];
   __shared__ uint32_t h0[1 << RADIX_MAX_BITS];  // digit counts of the first sort pass (bits 0 .. log2 nb0)
+  __shared__ int32_t wmax[INGEST_THREADS / 64];
   const int64_t NB = (int64_t)T * B;
   // tiles in order, an eighth per XCD, as the sort's first pass takes them: that pass
-  // reads a tile's keys and positions on the XCD that wrote them
+  // reads a tile's keys on the XCD that wrote them
   const int tile = (int)xcd_block(blockIdx.x, gridDim.x);
   if (tile >= ntiles) return;
   const int64_t o0 = (int64_t)tile * SORT_TILE;
   const int64_t o1 = (o0 + SORT_TILE < M ? o0 + SORT_TILE : M);
   // every index of the thread's items is loaded before any is used, and before the
-  // bag window, so the loads are in flight together
-  int64_t gv[SORT_ITEMS];
+  // bags' starts, so the loads are in flight together
+  int64_t gv[INGEST_ITEMS];
 #pragma unroll
-  for (int j = 0; j < SORT_ITEMS; ++j) {
-    const int64_t o = o0 + (int64_t)j * SORT_THREADS + threadIdx.x;
+  for (int j = 0; j < INGEST_ITEMS; ++j) {
+    const int64_t o = o0 + (int64_t)j * INGEST_THREADS + threadIdx.x;
     gv[j] = o < o1 ? __builtin_nontemporal_load(idx + o) : 0;
   }
   if (counts0)
-    for (int d = threadIdx.x; d < nb0; d += SORT_THREADS) h0[d] = 0u;
-  int64_t bfirst = 0, nwin = 0;
+    for (int d = threadIdx.x; d < nb0; d += INGEST_THREADS) h0[d] = 0u;
+  int64_t f = o0, l = o1 - 1;  // first and last bag of the tile
+  bool marked = false;
   if (offsets) {
-    // bags of this tile: from the bag holding o0 to the one holding the next tile's first occurrence
-    int64_t f = tile_bag[tile];
-    int64_t l = o1 < M ? (int64_t)tile_bag[tile + 1] : NB - 1;
+    // from the bag holding o0 to the one holding the next tile's first occurrence
+    f = tile_bag[tile];
+    l = o1 < M ? (int64_t)tile_bag[tile + 1] : NB - 1;
     f = f < 0 ? 0 : (f > NB - 1 ? NB - 1 : f);
     l = l < f ? f : (l > NB - 1 ? NB - 1 : l);
-    bfirst = f;
-    nwin = l - f + 2;  // offsets[bfirst .. l + 1]
-    if (nwin <= INGEST_WIN)
-      for (int k = threadIdx.x; k < nwin; k += SORT_THREADS) win[k] = offsets[bfirst + k];
+    marked = l - f <= INGEST_WIN;
+    if (marked) {
+      for (int k = threadIdx.x; k < SORT_TILE; k += INGEST_THREADS) mark[k] = 0;
+      __syncthreads();
+      for (int64_t b = f + 1 + threadIdx.x; b <= l; b += INGEST_THREADS) {
+        const int64_t s0 = offsets[b];
+        if (s0 >= o0 && s0 < o1) atomicMax(&mark[s0 - o0], (int32_t)(b - f));
+      }
+      __syncthreads();
+      // running maximum: a thread's INGEST_ITEMS consecutive marks, then the threads before it
+      int32_t m[INGEST_ITEMS];
+      const int e0 = (int)threadIdx.x * INGEST_ITEMS;
+#pragma unroll
+      for (int k = 0; k < INGEST_ITEMS; ++k) {
+        m[k] = mark[e0 + k];
+        if (k && m[k - 1] > m[k]) m[k] = m[k - 1];
+      }
+      const int lane = lane_id(), w = threadIdx.x >> 6;
+      int32_t run = m[INGEST_ITEMS - 1];
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const int32_t u = __shfl_up(run, o, 64);
+        if (lane >= o && u > run) run = u;
+      }
+      if (lane == 63) wmax[w] = run;
+      int32_t before = __shfl_up(run, 1, 64);
+      if (lane == 0) before = 0;
+      __syncthreads();
+      for (int k = 0; k < w; ++k) before = wmax[k] > before ? wmax[k] : before;
+#pragma unroll
+      for (int k = 0; k < INGEST_ITEMS; ++k) mark[e0 + k] = m[k] > before ? m[k] : before;
+    }
   }
-  __syncthreads();  // the bag window and the cleared digit counts
+  __syncthreads();  // the marks and the cleared digit counts
+  const uint32_t t0 = quot((uint32_t)f, divB);
+  const bool one_table = t0 == quot((uint32_t)l, divB);
   int err = 0;
 #pragma unroll
-  for (int j = 0; j < SORT_ITEMS; ++j) {
-    const int64_t o = o0 + (int64_t)j * SORT_THREADS + threadIdx.x;
+  for (int j = 0; j < INGEST_ITEMS; ++j) {
+    const int e = j * INGEST_THREADS + (int)threadIdx.x;
+    const int64_t o = o0 + e;
     if (o >= o1) break;
-    int64_t b;
-    if (!offsets) {
-      b = o;
-    } else if (nwin <= INGEST_WIN) {
-      int lo = 0, hi = (int)nwin;
-      while (lo < hi) {
-        const int mid = (lo + hi) >> 1;
-        if (win[mid] <= o)
-          lo = mid + 1;
-        else
-          hi = mid;
-      }
-      b = bfirst + lo - 1;
-    } else {
-      b = upper_bound_global(offsets, 0, NB + 1, o) - 1;
-    }
+    int64_t b = o;
+    if (offsets) b = marked ? f + mark[e] : upper_bound_global(offsets, 0, NB + 1, o) - 1;
     b = b < 0 ? 0 : (b > NB - 1 ? NB - 1 : b);
     const int64_t g = gv[j];
-    const uint32_t t = (uint32_t)b / (uint32_t)B;
+    const uint32_t t = one_table && (marked || !offsets) ? t0 : quot((uint32_t)b, divB);
     uint32_t key;
     if (g >= 0 && g < N) {
       key = t * Npad + (uint32_t)g;
@@ -139,14 +165,13 @@ __global__ void __launch_bounds__(SORT_THREADS) k_ingest(const int64_t* __restri
       err = 1;
     }
     keys[o] = key;
-    vals[o] = (uint32_t)o;
     __builtin_nontemporal_store((int32_t)b, bag_of + o);
     if (counts0) atomicAdd(&h0[key & (uint32_t)(nb0 - 1)], 1u);
   }
   if (err) atomicOr(&ctr[C_ERR], ERR_INDEX);
   if (counts0) {  // this tile's counts of the first pass, laid out as the histogram kernel's
     __syncthreads();
-    for (int d = threadIdx.x; d < nb0; d += SORT_THREADS) counts0[d * ntiles + tile] = h0[d];
+    for (int d = threadIdx.x; d < nb0; d += INGEST_THREADS) counts0[d * ntiles + tile] = h0[d];
   }
 }
 
@@ -166,10 +191,15 @@ __global__ void k_check_offsets(const int64_t* __restrict__ offsets, int64_t NB,
 // ---------------------------------------------------------------------------
 // LSD radix sort of (key, position), stable, BITS-bit digits (8..11)
 // ---------------------------------------------------------------------------
+// Waves per tile.  A pass ranks a wave's keys one after the other, so a tile of few waves is
+// a long chain, and four waves beside the tile's 42 KB of LDS left a CU with twelve; sixteen
+// pay more for the waves' digit counts.  4 / 8 / 16 waves: forward of the 8-table workload
+// (5.2M keys, 9-bit passes) 723 / 714 / 724 us, 32,768 single look-ups (8-bit) 100 / 93 / 92.
+constexpr int SORT_WAVES = 8;
 template <int BITS>
-__global__ void __launch_bounds__(SORT_THREADS) k_radix_hist(const uint32_t* __restrict__ keys, int n, int shift,
-                                                             uint32_t* __restrict__ counts, int ntiles) {
-  constexpr int NB = 1 << BITS;
+__global__ void __launch_bounds__(256) k_radix_hist(const uint32_t* __restrict__ keys, int n, int shift,
+                                                    uint32_t* __restrict__ counts, int ntiles) {
+  constexpr int NB = 1 << BITS, NT = 256, ITEMS = SORT_TILE / NT;
   __shared__ uint32_t h[4][NB];  // one histogram per wave
   // tiles in order, an eighth per XCD: the counts of 32 neighbouring tiles share a
   // cache line, written from one L2, and the scatter reads its tiles' keys again
@@ -177,36 +207,35 @@ __global__ void __launch_bounds__(SORT_THREADS) k_radix_hist(const uint32_t* __r
   const int tile = (int)xcd_block(blockIdx.x, gridDim.x);
   if (tile >= ntiles) return;
   const int w = threadIdx.x >> 6;
-  for (int k = threadIdx.x; k < 4 * NB; k += SORT_THREADS) (&h[0][0])[k] = 0;
+  for (int k = threadIdx.x; k < 4 * NB; k += NT) (&h[0][0])[k] = 0;
   __syncthreads();
   const int base = tile * SORT_TILE;
   if (base + SORT_TILE <= n) {
     // a full tile: the order of the counts does not matter, so 16-byte loads
     const uint4* k4 = reinterpret_cast<const uint4*>(keys + base) + threadIdx.x;
-    uint4 v[SORT_ITEMS / 4];
+    uint4 v[ITEMS / 4];
 #pragma unroll
-    for (int j = 0; j < SORT_ITEMS / 4; ++j) v[j] = k4[j * SORT_THREADS];
+    for (int j = 0; j < ITEMS / 4; ++j) v[j] = k4[j * NT];
 #pragma unroll
-    for (int j = 0; j < SORT_ITEMS / 4; ++j) {
+    for (int j = 0; j < ITEMS / 4; ++j) {
       atomicAdd(&h[w][(v[j].x >> shift) & (NB - 1)], 1u);
       atomicAdd(&h[w][(v[j].y >> shift) & (NB - 1)], 1u);
       atomicAdd(&h[w][(v[j].z >> shift) & (NB - 1)], 1u);
       atomicAdd(&h[w][(v[j].w >> shift) & (NB - 1)], 1u);
     }
   } else {
-    uint32_t k[SORT_ITEMS];
+    uint32_t k[ITEMS];
 #pragma unroll
-    for (int j = 0; j < SORT_ITEMS; ++j) {
-      const int i = base + j * SORT_THREADS + threadIdx.x;
+    for (int j = 0; j < ITEMS; ++j) {
+      const int i = base + j * NT + threadIdx.x;
       k[j] = i < n ? keys[i] : 0u;
     }
 #pragma unroll
-    for (int j = 0; j < SORT_ITEMS; ++j)
-      if (base + j * SORT_THREADS + (int)threadIdx.x < n) atomicAdd(&h[w][(k[j] >> shift) & (NB - 1)], 1u);
+    for (int j = 0; j < ITEMS; ++j)
+      if (base + j * NT + (int)threadIdx.x < n) atomicAdd(&h[w][(k[j] >> shift) & (NB - 1)], 1u);
   }
   __syncthreads();
-  for (int d = threadIdx.x; d < NB; d += SORT_THREADS)
-    counts[d * ntiles + tile] = h[0][d] + h[1][d] + h[2][d] + h[3][d];
+  for (int d = threadIdx.x; d < NB; d += NT) counts[d * ntiles + tile] = h[0][d] + h[1][d] + h[2][d] + h[3][d];
 }
 
 // one block per digit: exclusive offsets of every tile within that digit, and
@@ -240,55 +269,67 @@ __global__ void __launch_bounds__(256) k_radix_scan(uint32_t* __restrict__ count
   if (threadIdx.x == 0) totals[d] = running;
 }
 
-// Stable scatter.  Wave w of the block owns keys [tile + w*1024, +1024); item j
-// of lane l is element w*1024 + j*64 + l, so (w, j, l) order is input order.
+// Stable scatter.  Wave w of the block owns ITEMS * 64 consecutive keys of the tile; item j
+// of lane l is element j*64 + l of them, so (w, j, l) order is input order.
 // Ranks come from per-wave ballots; the tile is first placed in LDS in digit
 // order, then written out so that consecutive threads of one digit write
-// consecutive addresses.
-template <int BITS>
-__global__ void __launch_bounds__(SORT_THREADS) k_radix_scatter(const uint32_t* __restrict__ kin,
+// consecutive addresses.  vin null: the positions are the input order (the first pass of
+// the grouping's sort).  totals null: offs holds the raw tile counts, and the block sums
+// the tiles before its own itself (few tiles: one launch less per pass).
+template <int BITS, int W>
+__global__ void __launch_bounds__(64 * W) k_radix_scatter(const uint32_t* __restrict__ kin,
                                                                 const uint32_t* __restrict__ vin,
                                                                 uint32_t* __restrict__ kout,
                                                                 uint32_t* __restrict__ vout, int n, int shift,
                                                                 const uint32_t* __restrict__ offs, int ntiles,
                                                                 const uint32_t* __restrict__ totals) {
-  constexpr int NB = 1 << BITS;
-  __shared__ uint32_t wh[4][NB];  // per-wave digit counts, then the wave's local base per digit
+  constexpr int NB = 1 << BITS, NT = 64 * W, ITEMS = SORT_TILE / NT;
+  __shared__ uint32_t wh[W][NB];  // per-wave digit counts, then the wave's local base per digit
   __shared__ uint32_t dpos[NB];   // output position of the tile's first key of each digit, less
                                   // that key's position in the tile's digit order
   __shared__ uint32_t sk[SORT_TILE], sv[SORT_TILE];
-  __shared__ uint32_t scan_tmp[SORT_THREADS / 64];
+  __shared__ uint32_t scan_tmp[W];
   // tiles in order, an eighth per XCD (as in the histogram of the same pass)
   const int tile = (int)xcd_block(blockIdx.x, gridDim.x);
   if (tile >= ntiles) return;
   const int w = threadIdx.x >> 6;
   const int lane = lane_id();
-  for (int k = threadIdx.x; k < 4 * NB; k += SORT_THREADS) (&wh[0][0])[k] = 0;
+  for (int k = threadIdx.x; k < W * NB; k += NT) (&wh[0][0])[k] = 0;
   __syncthreads();
   const int tile0 = tile * SORT_TILE;
-  const int base = tile0 + w * (SORT_ITEMS * 64);
+  const int base = tile0 + w * (ITEMS * 64);
   const int nt = n - tile0 < SORT_TILE ? n - tile0 : SORT_TILE;  // keys in this tile
   const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-  uint32_t key[SORT_ITEMS], val[SORT_ITEMS], rk[SORT_ITEMS];
+  uint32_t key[ITEMS], val[ITEMS], rk[ITEMS];
 #pragma unroll
-  for (int j = 0; j < SORT_ITEMS; ++j) {
+  for (int j = 0; j < ITEMS; ++j) {
     const int i = base + j * 64 + lane;
     const bool ok = i < n;
     key[j] = ok ? kin[i] : 0u;
-    val[j] = ok ? vin[i] : 0u;
+    val[j] = vin ? (ok ? vin[i] : 0u) : (uint32_t)i;
   }
   // this tile's offset within each digit and the pass's digit totals, loaded with the
   // keys so that the write-out below needs no global read
-  constexpr int DPT = (NB + SORT_THREADS - 1) / SORT_THREADS;  // digits per thread
+  constexpr int DPT = (NB + NT - 1) / NT;  // digits per thread
   uint32_t toff[DPT], gt[DPT];
 #pragma unroll
   for (int q = 0; q < DPT; ++q) {
     const int d = threadIdx.x * DPT + q;
-    toff[q] = d < NB ? offs[d * ntiles + tile] : 0u;
-    gt[q] = d < NB ? totals[d] : 0u;
+    toff[q] = gt[q] = 0u;
+    if (d >= NB) continue;
+    if (totals) {
+      toff[q] = offs[d * ntiles + tile];
+      gt[q] = totals[d];
+    } else {
+      for (int x = 0; x < ntiles; ++x) {
+        const uint32_t v = offs[d * ntiles + x];
+        gt[q] += v;
+        if (x < tile) toff[q] += v;
+      }
+    }
   }
 #pragma unroll
-  for (int j = 0; j < SORT_ITEMS; ++j) {
+  for (int j = 0; j < ITEMS; ++j) {
     const int i = base + j * 64 + lane;
     const bool ok = i < n;
     const uint32_t dg = (key[j] >> shift) & (NB - 1);
@@ -310,34 +351,39 @@ __global__ void __launch_bounds__(SORT_THREADS) k_radix_scatter(const uint32_t* 
 #pragma unroll
   for (int q = 0; q < DPT; ++q) {
     const int d = threadIdx.x * DPT + q;
-    tot[q] = d < NB ? wh[0][d] + wh[1][d] + wh[2][d] + wh[3][d] : 0u;
+    tot[q] = 0u;
+    if (d < NB)
+#pragma unroll
+      for (int v = 0; v < W; ++v) tot[q] += wh[v][d];
     my += tot[q];
   }
   uint32_t all;
-  uint32_t run = block_excl_scan<uint32_t, SORT_THREADS>(my, scan_tmp, &all);
+  uint32_t run = block_excl_scan<uint32_t, NT>(my, scan_tmp, &all);
   // digit bases: exclusive scan of the digit totals of the whole pass
   uint32_t gmy = 0;
 #pragma unroll
   for (int q = 0; q < DPT; ++q) gmy += gt[q];
   uint32_t gall;
-  uint32_t grun = block_excl_scan<uint32_t, SORT_THREADS>(gmy, scan_tmp, &gall);
+  uint32_t grun = block_excl_scan<uint32_t, NT>(gmy, scan_tmp, &gall);
 #pragma unroll
   for (int q = 0; q < DPT; ++q) {
     const int d = threadIdx.x * DPT + q;
     if (d < NB) {
       dpos[d] = grun + toff[q] - run;
-      const uint32_t c0 = wh[0][d], c1 = wh[1][d], c2 = wh[2][d];
-      wh[0][d] = run;
-      wh[1][d] = run + c0;
-      wh[2][d] = run + c0 + c1;
-      wh[3][d] = run + c0 + c1 + c2;
+      uint32_t at = run;
+#pragma unroll
+      for (int v = 0; v < W; ++v) {
+        const uint32_t cnt = wh[v][d];
+        wh[v][d] = at;
+        at += cnt;
+      }
     }
     run += tot[q];
     grun += gt[q];
   }
   __syncthreads();
 #pragma unroll
-  for (int j = 0; j < SORT_ITEMS; ++j) {
+  for (int j = 0; j < ITEMS; ++j) {
     const int i = base + j * 64 + lane;
     if (i < n) {
       const uint32_t dg = (key[j] >> shift) & (NB - 1);
@@ -347,7 +393,7 @@ __global__ void __launch_bounds__(SORT_THREADS) k_radix_scatter(const uint32_t* 
     }
   }
   __syncthreads();
-  for (int p = threadIdx.x; p < nt; p += SORT_THREADS) {
+  for (int p = threadIdx.x; p < nt; p += NT) {
     const uint32_t k = sk[p];
     const uint32_t pos = dpos[(k >> shift) & (NB - 1)] + (uint32_t)p;
     kout[pos] = k;
@@ -359,33 +405,33 @@ __global__ void __launch_bounds__(SORT_THREADS) k_radix_scatter(const uint32_t* 
 // registers and LDS between passes.  Each pass ranks exactly as k_radix_scatter
 // does (wave ballots, per-wave digit counts, tile-local digit starts) and places
 // the tile in LDS in digit order, which for a single tile is the sorted order of
-// that pass.  Reads keys/vals and writes kout/vout (which may be the same arrays).
-template <int BITS>
-__global__ void __launch_bounds__(SORT_THREADS) k_sort_tile(const uint32_t* kin,
-                                                            const uint32_t* vin, uint32_t* kout,
+// that pass.  Reads keys (positions are the input order) and writes kout/vout (which may be
+// the same arrays).
+template <int BITS, int W>
+__global__ void __launch_bounds__(64 * W) k_sort_tile(const uint32_t* kin, uint32_t* kout,
                                                             uint32_t* vout, int n, int npasses, int dbits) {
-  constexpr int NB = 1 << BITS;
-  __shared__ uint32_t wh[4][NB];  // per-wave digit counts, then the wave's base per digit
+  constexpr int NB = 1 << BITS, NT = 64 * W, ITEMS = SORT_TILE / NT;
+  __shared__ uint32_t wh[W][NB];  // per-wave digit counts, then the wave's base per digit
   __shared__ uint32_t sk[SORT_TILE], sv[SORT_TILE];
-  __shared__ uint32_t scan_tmp[SORT_THREADS / 64];
+  __shared__ uint32_t scan_tmp[W];
   const int w = threadIdx.x >> 6;
   const int lane = lane_id();
-  const int base = w * (SORT_ITEMS * 64);
+  const int base = w * (ITEMS * 64);
   const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-  uint32_t key[SORT_ITEMS], val[SORT_ITEMS], rk[SORT_ITEMS];
+  uint32_t key[ITEMS], val[ITEMS], rk[ITEMS];
 #pragma unroll
-  for (int j = 0; j < SORT_ITEMS; ++j) {
+  for (int j = 0; j < ITEMS; ++j) {
     const int i = base + j * 64 + lane;
     const bool ok = i < n;
     key[j] = ok ? kin[i] : 0u;
-    val[j] = ok ? vin[i] : 0u;
+    val[j] = (uint32_t)i;
   }
   for (int p = 0; p < npasses; ++p) {
     const int shift = p * dbits;
-    for (int k = threadIdx.x; k < 4 * NB; k += SORT_THREADS) (&wh[0][0])[k] = 0;
+    for (int k = threadIdx.x; k < W * NB; k += NT) (&wh[0][0])[k] = 0;
     __syncthreads();
 #pragma unroll
-    for (int j = 0; j < SORT_ITEMS; ++j) {
+    for (int j = 0; j < ITEMS; ++j) {
       const int i = base + j * 64 + lane;
       const bool ok = i < n;
       const uint32_t dg = (key[j] >> shift) & (NB - 1);
@@ -402,31 +448,36 @@ __global__ void __launch_bounds__(SORT_THREADS) k_sort_tile(const uint32_t* kin,
       if (ok && before == 0) wh[w][dg] = prev + cnt;
     }
     __syncthreads();
-    constexpr int DPT = (NB + SORT_THREADS - 1) / SORT_THREADS;  // digits per thread
+    constexpr int DPT = (NB + NT - 1) / NT;  // digits per thread
     uint32_t tot[DPT], my = 0;
 #pragma unroll
     for (int q = 0; q < DPT; ++q) {
       const int d = threadIdx.x * DPT + q;
-      tot[q] = d < NB ? wh[0][d] + wh[1][d] + wh[2][d] + wh[3][d] : 0u;
+      tot[q] = 0u;
+      if (d < NB)
+#pragma unroll
+        for (int v = 0; v < W; ++v) tot[q] += wh[v][d];
       my += tot[q];
     }
     uint32_t all;
-    uint32_t run = block_excl_scan<uint32_t, SORT_THREADS>(my, scan_tmp, &all);
+    uint32_t run = block_excl_scan<uint32_t, NT>(my, scan_tmp, &all);
 #pragma unroll
     for (int q = 0; q < DPT; ++q) {
       const int d = threadIdx.x * DPT + q;
       if (d < NB) {
-        const uint32_t c0 = wh[0][d], c1 = wh[1][d], c2 = wh[2][d];
-        wh[0][d] = run;
-        wh[1][d] = run + c0;
-        wh[2][d] = run + c0 + c1;
-        wh[3][d] = run + c0 + c1 + c2;
+        uint32_t at = run;
+#pragma unroll
+        for (int v = 0; v < W; ++v) {
+          const uint32_t cnt = wh[v][d];
+          wh[v][d] = at;
+          at += cnt;
+        }
       }
       run += tot[q];
     }
     __syncthreads();
 #pragma unroll
-    for (int j = 0; j < SORT_ITEMS; ++j) {
+    for (int j = 0; j < ITEMS; ++j) {
       const int i = base + j * 64 + lane;
       if (i < n) {
         const uint32_t pos = wh[w][(key[j] >> shift) & (NB - 1)] + rk[j];
@@ -437,7 +488,7 @@ __global__ void __launch_bounds__(SORT_THREADS) k_sort_tile(const uint32_t* kin,
     __syncthreads();
     // element i of the pass's output is the next pass's input element i
 #pragma unroll
-    for (int j = 0; j < SORT_ITEMS; ++j) {
+    for (int j = 0; j < ITEMS; ++j) {
       const int i = base + j * 64 + lane;
       if (i < n) {
         key[j] = sk[i];
@@ -447,7 +498,7 @@ __global__ void __launch_bounds__(SORT_THREADS) k_sort_tile(const uint32_t* kin,
     __syncthreads();
   }
 #pragma unroll
-  for (int j = 0; j < SORT_ITEMS; ++j) {
+  for (int j = 0; j < ITEMS; ++j) {
     const int i = base + j * 64 + lane;
     if (i < n) {
       kout[i] = key[j];
@@ -477,12 +528,12 @@ __global__ void __launch_bounds__(SCAN_THREADS) k_scan_reduce(const T* __restric
 // The sum of v[0 .. count - 1] over the block (every thread gets it): a down-sweep
 // block forms its tile's offset from the raw tile totals itself, so no launch scans
 // the totals in between (integer sums: the order does not change them).
-template <typename T>
+template <typename T, int NT>
 __device__ __forceinline__ T block_sum_first(const T* __restrict__ v, int count, T* smem) {
   T s = 0;
-  for (int i = threadIdx.x; i < count; i += SCAN_THREADS) s += v[i];
+  for (int i = threadIdx.x; i < count; i += NT) s += v[i];
   T tot;
-  block_excl_scan<T, SCAN_THREADS>(s, smem, &tot);
+  block_excl_scan<T, NT>(s, smem, &tot);
   return tot;
 }
 
@@ -502,7 +553,7 @@ __global__ void __launch_bounds__(SCAN_THREADS) k_scan_down(const T* __restrict_
     v[k] = i < n ? in[i] : (T)0;
     s += v[k];
   }
-  const T before = tsum ? block_sum_first<T>(tsum, (int)blockIdx.x, smem) : (T)0;
+  const T before = tsum ? block_sum_first<T, SCAN_THREADS>(tsum, (int)blockIdx.x, smem) : (T)0;
   T tot;
   T acc = block_excl_scan<T, SCAN_THREADS>(s, smem, &tot) + before;
   if (total_out && blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) *total_out = (int32_t)(before + tot);
@@ -543,7 +594,7 @@ hipError_t scan_u32_exclusive(const uint32_t* in, uint32_t* out, int64_t n, uint
 // prefix group when, in addition, key / n3 (table and prefix) differs.  Counts
 // are packed (rows | groups << 32).
 __global__ void __launch_bounds__(SCAN_THREADS) k_group_reduce(const uint32_t* __restrict__ sk, int n, uint32_t kinv,
-                                                               uint32_t n3, int dedup, uint64_t* __restrict__ tsum,
+                                                               FastDiv n3, int dedup, uint64_t* __restrict__ tsum,
                                                                int32_t* __restrict__ ctr) {
   __shared__ uint64_t smem[SCAN_THREADS / 64];
   // each thread counts SCAN_ITEMS consecutive keys (16-byte loads), so a key's
@@ -567,12 +618,12 @@ __global__ void __launch_bounds__(SCAN_THREADS) k_group_reduce(const uint32_t* _
   const uint32_t kprev = e0 > 0 && e0 <= n ? sk[e0 - 1] : 0u;
   const uint32_t knext = e0 + SCAN_ITEMS < n ? sk[e0 + SCAN_ITEMS] : kinv;
   uint64_t c = 0;
-  uint32_t pprev = kprev / n3;
+  uint32_t pprev = quot(kprev, n3);
 #pragma unroll
   for (int q = 0; q < SCAN_ITEMS; ++q) {
     const int i = e0 + q;
     const uint32_t key = k[q], kp = q ? k[q - 1] : kprev;
-    const uint32_t pk = key / n3;
+    const uint32_t pk = quot(key, n3);
     if (i < n && key < kinv) {
       const bool head = i == 0 || kp != key || !dedup;
       const bool pgh = head && (i == 0 || pprev != pk);
@@ -592,10 +643,12 @@ __global__ void __launch_bounds__(SCAN_THREADS) k_group_reduce(const uint32_t* _
 // coalesced; writes the inverse map, row id per sorted occurrence, unique keys,
 // i3 per row, occurrence starts, prefix-group starts and keys.
 __device__ __forceinline__ int pad32(int x) { return x + (x >> 5); }
+// Threads per tile (256 / 512 / 1,024 on the 8-table forward: 732 / 724 / 724 us)
+constexpr int DOWN_THREADS = 512, DOWN_ITEMS = SCAN_TILE / DOWN_THREADS;
 
-__global__ void __launch_bounds__(SCAN_THREADS) k_group_down(const uint32_t* __restrict__ sk,
+__global__ void __launch_bounds__(DOWN_THREADS) k_group_down(const uint32_t* __restrict__ sk,
                                                              const uint32_t* __restrict__ sp, int n, uint32_t kinv,
-                                                             uint32_t n3, uint32_t Npad, int dedup,
+                                                             FastDiv n3, FastDiv Npad, int dedup,
                                                              const uint64_t* __restrict__ tsum,
                                                              int32_t* __restrict__ inv, int32_t* __restrict__ sorted_uid,
                                                              uint32_t* __restrict__ uniq_key,
@@ -604,11 +657,11 @@ __global__ void __launch_bounds__(SCAN_THREADS) k_group_down(const uint32_t* __r
                                                              int32_t* __restrict__ pg_start,
                                                              uint32_t* __restrict__ pg_key, int32_t* __restrict__ ctr) {
   // LDS index x is stored at x + x / 32 so that the per-thread runs of
-  // SCAN_ITEMS consecutive entries do not all fall on two banks
+  // DOWN_ITEMS consecutive entries do not all fall on two banks
   __shared__ uint32_t lk[SCAN_TILE + 2 + SCAN_TILE / 32];  // lk[e + 1] = key of tile element e, lk[0] = key before
   __shared__ int32_t lu[SCAN_TILE + SCAN_TILE / 32];        // row id of each element (-1: invalid)
   __shared__ int32_t lg[SCAN_TILE + SCAN_TILE / 32];        // (group id << 1) | group starts here; -1: invalid
-  __shared__ uint64_t smem[SCAN_THREADS / 64];
+  __shared__ uint64_t smem[DOWN_THREADS / 64];
   // tiles in sorted order, an eighth per XCD: a table's inverse-map entries (a
   // contiguous range of positions) are scattered within one XCD's L2, and the
   // kernel's sequential reads and writes are non-temporal so that they do not push
@@ -618,39 +671,42 @@ __global__ void __launch_bounds__(SCAN_THREADS) k_group_down(const uint32_t* __r
   const int base = tile * SCAN_TILE;
   // the positions of the thread's striped elements, loaded with the keys so that the
   // inverse-map stores below wait on no load
-  uint32_t pos[SCAN_ITEMS];
+  uint32_t pos[DOWN_ITEMS];
 #pragma unroll
-  for (int j = 0; j < SCAN_ITEMS; ++j) {
-    const int e = j * SCAN_THREADS + (int)threadIdx.x;
+  for (int j = 0; j < DOWN_ITEMS; ++j) {
+    const int e = j * DOWN_THREADS + (int)threadIdx.x;
     pos[j] = base + e < n ? __builtin_nontemporal_load(sp + base + e) : 0u;
   }
 #pragma unroll 4
-  for (int j = 0; j < SCAN_ITEMS; ++j) {
-    const int e = j * SCAN_THREADS + (int)threadIdx.x;
+  for (int j = 0; j < DOWN_ITEMS; ++j) {
+    const int e = j * DOWN_THREADS + (int)threadIdx.x;
     lk[pad32(e + 1)] = base + e < n ? __builtin_nontemporal_load(sk + base + e) : kinv;
   }
   if (threadIdx.x == 0) lk[0] = base > 0 ? sk[base - 1] : 0u;
   __syncthreads();
-  // run ids: each thread scans SCAN_ITEMS consecutive elements
-  const int e0 = (int)threadIdx.x * SCAN_ITEMS;
+  // run ids: each thread scans DOWN_ITEMS consecutive elements
+  const int e0 = (int)threadIdx.x * DOWN_ITEMS;
   uint32_t hb = 0, pb = 0;  // head / group-head bits of the thread's elements
+  uint32_t pprev = quot(lk[pad32(e0)], n3);
 #pragma unroll
-  for (int k = 0; k < SCAN_ITEMS; ++k) {
+  for (int k = 0; k < DOWN_ITEMS; ++k) {
     const int i = base + e0 + k;
     const uint32_t key = lk[pad32(e0 + k + 1)], kp = lk[pad32(e0 + k)];
+    const uint32_t pk = quot(key, n3);
     if (i < n && key < kinv) {
       const bool head = i == 0 || kp != key || !dedup;
-      const bool pgh = head && (i == 0 || kp / n3 != key / n3);
+      const bool pgh = head && (i == 0 || pprev != pk);
       hb |= (uint32_t)head << k;
       pb |= (uint32_t)pgh << k;
     }
+    pprev = pk;
   }
   uint64_t tot;
   const uint64_t c = (uint64_t)__popc(hb) | ((uint64_t)__popc(pb) << 32);
-  const uint64_t before = tsum ? block_sum_first<uint64_t>(tsum, tile, smem) : 0ull;
-  uint64_t acc = block_excl_scan<uint64_t, SCAN_THREADS>(c, smem, &tot) + before;
+  const uint64_t before = tsum ? block_sum_first<uint64_t, DOWN_THREADS>(tsum, tile, smem) : 0ull;
+  uint64_t acc = block_excl_scan<uint64_t, DOWN_THREADS>(c, smem, &tot) + before;
 #pragma unroll
-  for (int k = 0; k < SCAN_ITEMS; ++k) {
+  for (int k = 0; k < DOWN_ITEMS; ++k) {
     const int i = base + e0 + k;
     const uint32_t key = lk[pad32(e0 + k + 1)];
     acc += (uint64_t)((hb >> k) & 1) | ((uint64_t)((pb >> k) & 1) << 32);
@@ -661,8 +717,8 @@ __global__ void __launch_bounds__(SCAN_THREADS) k_group_down(const uint32_t* __r
   __syncthreads();
   // all global writes in striped order (consecutive lanes, consecutive elements)
 #pragma unroll
-  for (int j = 0; j < SCAN_ITEMS; ++j) {
-    const int e = j * SCAN_THREADS + (int)threadIdx.x;
+  for (int j = 0; j < DOWN_ITEMS; ++j) {
+    const int e = j * DOWN_THREADS + (int)threadIdx.x;
     const int i = base + e;
     if (i >= n) continue;
     const int32_t uid = lu[pad32(e)];
@@ -672,14 +728,15 @@ __global__ void __launch_bounds__(SCAN_THREADS) k_group_down(const uint32_t* __r
     const uint32_t key = lk[pad32(e + 1)], kp = lk[pad32(e)];
     if (i == 0 || kp != key || !dedup) {
       __builtin_nontemporal_store(key, uniq_key + uid);
-      __builtin_nontemporal_store((int)((key % Npad) % n3), uniq_i3 + uid);
+      const uint32_t g = key - quot(key, Npad) * Npad.d;  // the row; then its last digit
+      __builtin_nontemporal_store((int)(g - quot(g, n3) * n3.d), uniq_i3 + uid);
       __builtin_nontemporal_store(i, occ_start + uid);
     }
     const int32_t gv = lg[pad32(e)];
     const int32_t pg = gv >> 1;
     if (gv & 1) {
       pg_start[pg] = uid;
-      pg_key[pg] = key / n3;
+      pg_key[pg] = quot(key, n3);
     }
     const uint32_t knext = e + 1 < SCAN_TILE ? lk[pad32(e + 2)] : (i + 1 < n ? sk[i + 1] : kinv);
     if (i == n - 1 || knext >= kinv) {
@@ -880,19 +937,30 @@ static int grid_for(int64_t n, int per_block, int cap) {
   return (int)g;
 }
 
-// counted: the tile counts of this pass are already in rcounts (the first pass of
-// the grouping's sort, counted by the ingest kernel)
+// Up to FEW_TILES tiles a scatter block sums the raw tile counts itself, in place of the
+// scan launch: at most that many loads in flight per digit.
+constexpr int FEW_TILES = 32;
+// first: the first pass of the grouping's sort, whose tile counts are already in rcounts
+// (counted by the ingest kernel) and whose positions are the input order
 template <int BITS>
 static hipError_t radix_pass(const Work& w, int cur, int n, int shift, int ntiles, uint32_t* tot, hipStream_t st,
-                             bool counted = false) {
-  if (!counted)
-    hipLaunchKernelGGL(k_radix_hist<BITS>, dim3(xcd_grid(ntiles)), dim3(SORT_THREADS), 0, st, w.keys[cur], n, shift,
-                       w.rcounts, ntiles);
-  hipLaunchKernelGGL(k_radix_scan, dim3(1 << BITS), dim3(256), 0, st, w.rcounts, ntiles, tot);
-  hipLaunchKernelGGL(k_radix_scatter<BITS>, dim3(xcd_grid(ntiles)), dim3(SORT_THREADS), 0, st, w.keys[cur], w.vals[cur],
-                     w.keys[cur ^ 1], w.vals[cur ^ 1], n, shift, (const uint32_t*)w.rcounts, ntiles,
-                     (const uint32_t*)tot);
+                             bool first = false) {
+  constexpr int W = SORT_WAVES;
+  if (!first)
+    hipLaunchKernelGGL(k_radix_hist<BITS>, dim3(xcd_grid(ntiles)), dim3(256), 0, st, w.keys[cur], n, shift, w.rcounts,
+                       ntiles);
+  const bool few = ntiles <= FEW_TILES;
+  if (!few) hipLaunchKernelGGL(k_radix_scan, dim3(1 << BITS), dim3(256), 0, st, w.rcounts, ntiles, tot);
+  hipLaunchKernelGGL((k_radix_scatter<BITS, W>), dim3(xcd_grid(ntiles)), dim3(64 * W), 0, st, w.keys[cur],
+                     first ? (const uint32_t*)nullptr : w.vals[cur], w.keys[cur ^ 1], w.vals[cur ^ 1], n, shift,
+                     (const uint32_t*)w.rcounts, ntiles, few ? (const uint32_t*)nullptr : (const uint32_t*)tot);
   return hipGetLastError();
+}
+template <int BITS>
+static void sort_tile(const Work& w, int cur, int n, int npasses, int dbits, hipStream_t st) {
+  constexpr int W = SORT_WAVES;
+  hipLaunchKernelGGL((k_sort_tile<BITS, W>), dim3(1), dim3(64 * W), 0, st, w.keys[0], w.keys[cur], w.vals[cur], n,
+                     npasses, dbits);
 }
 
 // Stable LSD radix sort of n (key, value) pairs of key_bits-bit keys between the
@@ -960,23 +1028,19 @@ hipError_t launch_group(const Shape& s, const Work& w, const int64_t* idx, int64
                        w.tile_bag, w.ctr);
   // with more than one tile, ingest also counts the digits of the first sort pass
   const bool count0 = ntiles > 1 && npasses > 0;
-  hipLaunchKernelGGL(k_ingest, dim3(xcd_grid(ntiles)), dim3(SORT_THREADS), 0, st, idx, M, offsets, (const int32_t*)w.tile_bag,
-                     B, s.T, s.N, s.Npad, s.kinv, w.keys[0], w.vals[0], w.bag_of, w.ctr, count0 ? w.rcounts : nullptr,
-                     radix, ntiles);
+  hipLaunchKernelGGL(k_ingest, dim3(xcd_grid(ntiles)), dim3(INGEST_THREADS), 0, st, idx, M, offsets,
+                     (const int32_t*)w.tile_bag, B, s.T, s.N, s.Npad, s.kinv, fast_div_of((uint32_t)B), w.keys[0],
+                     w.bag_of, w.ctr, count0 ? w.rcounts : nullptr, radix, ntiles);
   prof_end(prof, K_INGEST, st);
   int cur = 0;
   if (ntiles == 1) {
     // one tile: all passes in one launch, the result where the last pass would leave it
     cur = npasses & 1;
     switch (bits) {
-      case 8: hipLaunchKernelGGL(k_sort_tile<8>, dim3(1), dim3(SORT_THREADS), 0, st, w.keys[0], w.vals[0],
-                                 w.keys[cur], w.vals[cur], n, npasses, dbits); break;
-      case 9: hipLaunchKernelGGL(k_sort_tile<9>, dim3(1), dim3(SORT_THREADS), 0, st, w.keys[0], w.vals[0],
-                                 w.keys[cur], w.vals[cur], n, npasses, dbits); break;
-      case 10: hipLaunchKernelGGL(k_sort_tile<10>, dim3(1), dim3(SORT_THREADS), 0, st, w.keys[0], w.vals[0],
-                                  w.keys[cur], w.vals[cur], n, npasses, dbits); break;
-      default: hipLaunchKernelGGL(k_sort_tile<11>, dim3(1), dim3(SORT_THREADS), 0, st, w.keys[0], w.vals[0],
-                                  w.keys[cur], w.vals[cur], n, npasses, dbits); break;
+      case 8: sort_tile<8>(w, cur, n, npasses, dbits, st); break;
+      case 9: sort_tile<9>(w, cur, n, npasses, dbits, st); break;
+      case 10: sort_tile<10>(w, cur, n, npasses, dbits, st); break;
+      default: sort_tile<11>(w, cur, n, npasses, dbits, st); break;
     }
   } else {
     for (int p = 0; p < npasses; ++p) {
@@ -997,10 +1061,10 @@ hipError_t launch_group(const Shape& s, const Work& w, const int64_t* idx, int64
   {
     const int gt = (n + SCAN_TILE - 1) / SCAN_TILE;
     if (gt > 1) {  // a single tile starts at row 0 and group 0: no tile offsets needed
-      hipLaunchKernelGGL(k_group_reduce, dim3(gt), dim3(SCAN_THREADS), 0, st, sk, n, s.kinv, (uint32_t)s.n3, s.dedup,
+      hipLaunchKernelGGL(k_group_reduce, dim3(gt), dim3(SCAN_THREADS), 0, st, sk, n, s.kinv, fast_div_of(s.n3), s.dedup,
                          w.tsum64, w.ctr);
     }
-    hipLaunchKernelGGL(k_group_down, dim3(xcd_grid(gt)), dim3(SCAN_THREADS), 0, st, sk, sp, n, s.kinv, (uint32_t)s.n3, s.Npad,
+    hipLaunchKernelGGL(k_group_down, dim3(xcd_grid(gt)), dim3(DOWN_THREADS), 0, st, sk, sp, n, s.kinv, fast_div_of(s.n3), fast_div_of(s.Npad),
                        s.dedup, gt > 1 ? (const uint64_t*)w.tsum64 : nullptr, w.inv, w.sorted_uid, w.uniq_key,
                        w.uniq_i3, w.occ_start, w.pg_start, w.pg_key, w.ctr);
   }

@@ -99,3 +99,20 @@ def test_chunk_lengths(lib, orc, d, R, n1):
                       sigma=0.3)
     emb = _check(lib, orc, case, f"chunks n1={n1} {d} R={R}")
     assert emb.counts()["nslices"] > (1000 if n1 == 5 else 40000)
+
+
+# bags of one tile beyond, at and below what the ingest kernel marks in LDS (16,384 bags of a
+# 4,096-occurrence tile), and radix passes with their scan launch and without (32 tiles)
+@pytest.mark.parametrize("bags,filled", [(40000, 50), (16385, 16385), (16384, 300), (32 * 4096, 32 * 4096),
+                                         (32 * 4096 + 1, 32 * 4096 + 1)])
+def test_grouping_bag_and_tile_edges(lib, orc, bags, filled):
+    rng = np.random.default_rng(bags)
+    lens = np.zeros(bags, np.int64)
+    lens[np.sort(rng.choice(bags, filled, replace=False))] = rng.integers(1, 9, filled) if filled < 1000 else 1
+    case = ttgen.tiny(8500, 1, (20, 30, 40), (2, 2, 2), 4, B=bags, max_len=1)
+    case["offsets"] = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    case["idx"] = rng.integers(0, 20 * 30 * 40, int(lens.sum())).astype(np.int64)
+    emb = _check(lib, orc, case, f"{bags} bags")
+    got, ref = emb.debug_grouping(case["idx"].size), orc.grouping(case)
+    for k in ("inv", "occ_start", "occ_pos", "pg_start"):
+        assert np.array_equal(got[k], ref[k]), k
