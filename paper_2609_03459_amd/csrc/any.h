@@ -761,7 +761,6 @@ static const void* bwd_any_kernel(int d3) {
   }
 }
 
-// The claim counters must be zero.
 hipError_t launch_bwd_any(const Shape& s, const Work& w, const float* G1, const float* G2, const float* G3,
                           const Prof& prof, hipStream_t st) {
   AnyArgs a = any_args(s);

@@ -708,7 +708,9 @@ constexpr int G1_WIN = 2048;
 __global__ void __launch_bounds__(GRED_THREADS) k_gred_g1(ShapeArgs s, const uint32_t* __restrict__ dense_cnt,
                                                           const uint32_t* __restrict__ dense_base,
                                                           const float* __restrict__ dApart, float* __restrict__ dG1,
-                                                          float lr, bool update) {
+                                                          float lr, bool update, int32_t* __restrict__ ctr) {
+  // the fused backward is done with its claim counters: zero again for the next one
+  if (blockIdx.x + blockIdx.y == 0 && threadIdx.x < SCHED_NQ) ctr[C_BWD_CTR + threadIdx.x * SCHED_STRIDE] = 0;
   __shared__ uint32_t wsum[GRED_THREADS / 64];
   __shared__ uint32_t list[G1_WIN];
   const int ti1 = blockIdx.x;
@@ -777,16 +779,30 @@ __global__ void k_g3_bins(const uint32_t* __restrict__ keys, const int32_t* __re
   }
 }
 
-// dG3[t][i3] = sum of the dD partials of the rows of (t, i3), in row order
+// dG3[t][i3] = sum of the dD partials of the rows of (t, i3), in row order; the bin's range of
+// `rows` from the rows per bin (totals), or else from lo and hi
 __global__ void __launch_bounds__(GRED_THREADS) k_gred_g3(const int32_t* __restrict__ lo,
                                                           const int32_t* __restrict__ hi,
                                                           const uint32_t* __restrict__ rows,
+                                                          const uint32_t* __restrict__ totals,
                                                           const float* __restrict__ dDpart, int RD,
                                                           float* __restrict__ dG3, float lr, bool update) {
+  __shared__ uint32_t smem[GRED_THREADS / 64];
   const int b = blockIdx.x;
   const int e = blockIdx.y * GRED_THREADS + threadIdx.x;
+  int k0, k1;
+  if (totals) {  // the bin's rows follow those of the bins before it
+    uint32_t before = 0;
+    for (int x = threadIdx.x; x < b; x += GRED_THREADS) before += totals[x];
+    uint32_t sum;
+    block_excl_scan<uint32_t, GRED_THREADS>(before, smem, &sum);
+    k0 = (int)sum;
+    k1 = k0 + (int)totals[b];
+  } else {
+    k0 = lo[b];
+    k1 = hi[b];
+  }
   if (e >= RD) return;
-  const int k0 = lo[b], k1 = hi[b];
   float a[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   int k = k0;
   for (; k + 8 <= k1; k += 8) {
@@ -818,19 +834,29 @@ static hipError_t launch_partial_sums(const Shape& s, const Work& w, int64_t M, 
   const int d1R = s.d1 * s.R, RD = s.R * s.d3;
   const int n = (int)M;
   const uint32_t nbins = (uint32_t)s.T * (uint32_t)s.n3;
-  hipLaunchKernelGGL(k_g3_keys, dim3((n + 255) / 256 < 4096 ? (n + 255) / 256 : 4096), dim3(256), 0, st,
-                     shape_args(s), (const uint32_t*)w.uniq_key, (const int32_t*)w.ctr, n, nbins, w.g3keys[0],
-                     w.g3vals[0]);
-  int res = 0;
-  hipError_t e = sort_pairs(w, w.g3keys, w.g3vals, n, bits_of(nbins), &res, st);
-  if (e != hipSuccess) return e;
-  if ((e = fill_u32(reinterpret_cast<uint32_t*>(w.g3lo), nbins, 0u, st)) != hipSuccess) return e;
-  if ((e = fill_u32(reinterpret_cast<uint32_t*>(w.g3hi), nbins, 0u, st)) != hipSuccess) return e;
-  hipLaunchKernelGGL(k_g3_bins, dim3((n + 255) / 256 < 4096 ? (n + 255) / 256 : 4096), dim3(256), 0, st,
-                     (const uint32_t*)w.g3keys[res], (const int32_t*)w.ctr, w.g3lo, w.g3hi);
+  hipError_t e;
+  const uint32_t *rows = w.g3vals[0], *totals = nullptr;
+  if (nbins <= (uint32_t)RADIX_MAX) {
+    // one radix pass on the rows' keys as they stand (against keys, sort, clears and bin
+    // ranges as launches of their own, the hot-prefix training step 991 -> 976 us, d = (4, 4, 4),
+    // R = 16 at 655k look-ups 541 -> 532)
+    if ((e = sort_rows_by_i3(s, w, n, w.g3vals[0], st)) != hipSuccess) return e;
+    totals = w.rtotals;
+  } else {
+    hipLaunchKernelGGL(k_g3_keys, dim3((n + 255) / 256 < 4096 ? (n + 255) / 256 : 4096), dim3(256), 0, st,
+                       shape_args(s), (const uint32_t*)w.uniq_key, (const int32_t*)w.ctr, n, nbins, w.g3keys[0],
+                       w.g3vals[0]);
+    int res = 0;
+    if ((e = sort_pairs(w, w.g3keys, w.g3vals, n, bits_of(nbins), &res, st)) != hipSuccess) return e;
+    if ((e = fill_u32(reinterpret_cast<uint32_t*>(w.g3lo), nbins, 0u, st)) != hipSuccess) return e;
+    if ((e = fill_u32(reinterpret_cast<uint32_t*>(w.g3hi), nbins, 0u, st)) != hipSuccess) return e;
+    hipLaunchKernelGGL(k_g3_bins, dim3((n + 255) / 256 < 4096 ? (n + 255) / 256 : 4096), dim3(256), 0, st,
+                       (const uint32_t*)w.g3keys[res], (const int32_t*)w.ctr, w.g3lo, w.g3hi);
+    rows = w.g3vals[res];
+  }
   hipLaunchKernelGGL(k_gred_g3, dim3(nbins, (RD + GRED_THREADS - 1) / GRED_THREADS), dim3(GRED_THREADS), 0, st,
-                     (const int32_t*)w.g3lo, (const int32_t*)w.g3hi, (const uint32_t*)w.g3vals[res],
-                     (const float*)w.dDpart, RD, dG3, lr, update);
+                     (const int32_t*)w.g3lo, (const int32_t*)w.g3hi, rows, totals, (const float*)w.dDpart, RD, dG3, lr,
+                     update);
   if (s.L != 2) {
     e = bwd_r64_supported(s, w.M) ? launch_dg2_r64(s, w, G1, dG2, lr, update, st)
                                   : launch_dg2_any(s, w, G1, dG2, lr, update, st);
@@ -838,7 +864,7 @@ static hipError_t launch_partial_sums(const Shape& s, const Work& w, int64_t M, 
   }
   hipLaunchKernelGGL(k_gred_g1, dim3(s.T * s.n1, (d1R + GRED_THREADS - 1) / GRED_THREADS), dim3(GRED_THREADS), 0, st,
                      shape_args(s), (const uint32_t*)w.dense_cnt, (const uint32_t*)w.dense_base,
-                     (const float*)w.dApart, dG1, lr, update);
+                     (const float*)w.dApart, dG1, lr, update, w.ctr);
   return hipGetLastError();
 }
 
@@ -901,8 +927,6 @@ hipError_t launch_backward(const Shape& s, const Work& w, const float* G1, const
     return launch_partial_sums(s, w, M, G1, dG1, dG2, dG3, lr, update, st);
   }
   const int grid = persistent_grid() * 2;
-  if ((e = fill_u32(reinterpret_cast<uint32_t*>(w.ctr + C_BWD_CTR), SCHED_NQ * SCHED_STRIDE, 0u, st)) != hipSuccess)
-    return e;
   if (s.sched != SCHED_STEAL_CKPT) {
     if ((e = launch_bwd_any(s, w, G1, G2, G3, prof, st)) != hipSuccess) return e;
     return launch_partial_sums(s, w, M, G1, dG1, dG2, dG3, lr, update, st);

@@ -703,8 +703,11 @@ __global__ void __launch_bounds__(RED_THREADS) k_reduce_grads(ShapeArgs s, const
                                                               const float* __restrict__ dBpart, int nch_cap,
                                                               const float* __restrict__ g3part, int nwg,
                                                               float* __restrict__ dG1, float* __restrict__ dG2,
-                                                              float* __restrict__ dG3, float lr, bool update) {
+                                                              float* __restrict__ dG3, float lr, bool update,
+                                                              int32_t* __restrict__ ctr) {
   const int b = blockIdx.x;
+  // the fused backward is done with its claim counters (2 T owners): zero again for the next one
+  if (b == 0 && (int)threadIdx.x < 2 * s.T) ctr[C_BWD_CTR + threadIdx.x * SCHED_STRIDE] = 0;
   const int per_q = (s.n3 * 16 * D3 + RED_THREADS - 1) / RED_THREADS;
   const int n3b = 2 * s.T * per_q, n1b = s.T * s.n1;
   if (b < n3b) {
@@ -736,12 +739,10 @@ hipError_t launch_bwd_r32(const Shape& s, const Work& w, const float* G1, const 
   if (per_q < 1) per_q = 1;
   const int grid = nq * per_q;
   if (grid > MAX_BWD_WG || nq * SCHED_STRIDE > C_TOTAL - C_BWD_CTR) return hipErrorInvalidValue;
-  hipError_t e = fill_u32(reinterpret_cast<uint32_t*>(w.ctr + C_BWD_CTR), nq * SCHED_STRIDE, 0u, st);
-  if (e != hipSuccess) return e;
   const bool d8 = s.d3 == 8;
   const size_t lds = sizeof(float) * (d8 ? (size_t)s.n3 * 128 : (size_t)(s.n3 + 8) * 36) + sizeof(float) * BW_WAVES * BW_SCR;
   const void* kfn = d8 ? (const void*)k_bwd_r32<8> : (const void*)k_bwd_r32<2>;
-  e = hipFuncSetAttribute(kfn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  hipError_t e = hipFuncSetAttribute(kfn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
   prof_begin(prof, K_BWD_FUSED, st);
   hipLaunchKernelGGL(d8 ? k_bwd_r32<8> : k_bwd_r32<2>, dim3(grid), dim3(64 * BW_WAVES), lds, st, shape_args(s), G1, G2, G3,
@@ -753,7 +754,7 @@ hipError_t launch_bwd_r32(const Shape& s, const Work& w, const float* G1, const 
   hipLaunchKernelGGL(d8 ? k_reduce_grads<8> : k_reduce_grads<2>, dim3(red_blocks), dim3(RED_THREADS), 0, st, shape_args(s),
                      (const uint32_t*)w.dense_cnt, (const uint32_t*)w.dense_base, (const float*)w.dApart,
                      (int)w.nsl_max, (const uint32_t*)w.run_nch, (const float*)w.dBpart, (int)w.nch_max,
-                     (const float*)w.g3part, grid, dG1, dG2, dG3, lr, update);
+                     (const float*)w.g3part, grid, dG1, dG2, dG3, lr, update, w.ctr);
   return hipGetLastError();
 }
 

@@ -244,8 +244,6 @@ bool bwd_r64_supported(const Shape& s, int64_t max_indices) {
 
 hipError_t launch_bwd_r64(const Shape& s, const Work& w, const float* G1, const float* G2, const float* G3,
                           const Prof& prof, hipStream_t st) {
-  hipError_t e = fill_u32(reinterpret_cast<uint32_t*>(w.ctr + C_BWD_CTR), SCHED_NQ * SCHED_STRIDE, 0u, st);
-  if (e != hipSuccess) return e;
   const int blocks = persistent_grid() * B64_WG_PER_CU;
   prof_begin(prof, K_BWD_FUSED, st);
   hipLaunchKernelGGL(k_bwd_r64, dim3(blocks), dim3(64 * B64_WAVES), 0, st, shape_args(s), G1, G2, G3,

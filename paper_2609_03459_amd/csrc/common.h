@@ -49,8 +49,10 @@ enum : int {
   C_ERR = 4,      // sticky error bits
   C_NSEG = 5,     // occurrence chunks of the dE segment sums
   C_NCHUNKS = 8,    // chunks of the specialised kernels
-  C_FWD_CTR = 64,         // queue counters of the forward scheduler (stride SCHED_STRIDE)
-  C_BWD_CTR = 64 + 4096,  // queue counters of the backward scheduler (stride SCHED_STRIDE)
+  // queue counters of the schedulers (stride SCHED_STRIDE): zeroed by a grouping, and by the
+  // kernels that follow the fused ones
+  C_FWD_CTR = 64,
+  C_BWD_CTR = 64 + 4096,
   C_TOTAL = 64 + 2 * 4096,
 };
 enum : int { ERR_INDEX = 1, ERR_OFFSETS = 2 };
@@ -217,6 +219,10 @@ hipError_t launch_bwd_any(const Shape& s, const Work& w, const float* G1, const 
                           const Prof& prof, hipStream_t st);
 hipError_t launch_dg2_any(const Shape& s, const Work& w, const float* G1, float* dG2, float lr, bool update,
                           hipStream_t st);
+
+// The unique rows (at most n) in (table, i3) order, stable, for T n3 <= RADIX_MAX bins in one
+// radix pass: row ids into rows, the rows of every bin into w.rtotals (group.hip).
+hipError_t sort_rows_by_i3(const Shape& s, const Work& w, int n, uint32_t* rows, hipStream_t st);
 
 // Small generic kernels shared across units (defined in group.hip).
 hipError_t fill_u32(uint32_t* p, int64_t n, uint32_t v, hipStream_t st);

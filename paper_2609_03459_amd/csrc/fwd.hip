@@ -756,11 +756,18 @@ __global__ void __launch_bounds__(64 * F64_WAVES, F64_WG_PER_CU)
   }
 }
 
+// The pooling follows the fused forward, which is done with its claim counters then: zero
+// again for the next one (a grouping clears them first).
+__device__ __forceinline__ void reset_fwd_claims(int32_t* __restrict__ ctr) {
+  if (blockIdx.x == 0 && threadIdx.x < SCHED_NQ) ctr[C_FWD_CTR + threadIdx.x * SCHED_STRIDE] = 0;
+}
+
 // Sum pooling: LPB lanes per bag, float4 columns, occurrences in position order.
 template <int LPB>
 __global__ void __launch_bounds__(256) k_pool4(const float4* __restrict__ E, const int32_t* __restrict__ inv,
                                                const int64_t* __restrict__ offsets, int64_t M, int64_t NB, int D4,
-                                               float4* __restrict__ out) {
+                                               float4* __restrict__ out, int32_t* __restrict__ ctr) {
+  reset_fwd_claims(ctr);
   const int64_t gb = (int64_t)blockIdx.x * (256 / LPB) + threadIdx.x / LPB;
   const int sub = threadIdx.x % LPB;
   if (gb >= NB) return;
@@ -804,7 +811,8 @@ __global__ void __launch_bounds__(256) k_pool4(const float4* __restrict__ E, con
 // flight before they are summed in occurrence order.
 __global__ void __launch_bounds__(256) k_pool128(const float4* __restrict__ E, const int32_t* __restrict__ inv,
                                                  const int64_t* __restrict__ offsets, int64_t M, int64_t NB,
-                                                 float4* __restrict__ out) {
+                                                 float4* __restrict__ out, int32_t* __restrict__ ctr) {
+  reset_fwd_claims(ctr);
   const int lane = lane_id();
   const int half = lane >> 5, sub = lane & 31;
   const int64_t gb = ((int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) * 2 + half;
@@ -856,7 +864,8 @@ __global__ void __launch_bounds__(256) k_pool128(const float4* __restrict__ E, c
 
 __global__ void __launch_bounds__(256) k_pool1(const float* __restrict__ E, const int32_t* __restrict__ inv,
                                                const int64_t* __restrict__ offsets, int64_t M, int64_t NB, int D,
-                                               float* __restrict__ out) {
+                                               float* __restrict__ out, int32_t* __restrict__ ctr) {
+  reset_fwd_claims(ctr);
   const int64_t gb = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (gb >= NB) return;
   int64_t lo, hi;
@@ -893,13 +902,13 @@ int persistent_grid() {
 }
 
 hipError_t launch_pool(const Shape& s, const float* E, const int32_t* inv, const int64_t* offsets, int64_t M,
-                       int64_t B, float* out, const Prof& prof, hipStream_t st) {
+                       int64_t B, float* out, int32_t* ctr, const Prof& prof, hipStream_t st) {
   const int64_t NB = (int64_t)s.T * B;
   if (NB <= 0) return hipSuccess;
   prof_begin(prof, K_POOL, st);
   if (s.D == 128) {
     hipLaunchKernelGGL(k_pool128, dim3((unsigned)((NB + 7) / 8)), dim3(256), 0, st,
-                       reinterpret_cast<const float4*>(E), inv, offsets, M, NB, reinterpret_cast<float4*>(out));
+                       reinterpret_cast<const float4*>(E), inv, offsets, M, NB, reinterpret_cast<float4*>(out), ctr);
   } else if (s.D % 4 == 0) {
     const int D4 = s.D / 4;
     int lpb = 1;
@@ -909,16 +918,16 @@ hipError_t launch_pool(const Shape& s, const float* E, const int32_t* inv, const
     const float4* E4 = reinterpret_cast<const float4*>(E);
     float4* o4 = reinterpret_cast<float4*>(out);
     switch (lpb) {
-      case 1: hipLaunchKernelGGL(k_pool4<1>, grid, dim3(256), 0, st, E4, inv, offsets, M, NB, D4, o4); break;
-      case 2: hipLaunchKernelGGL(k_pool4<2>, grid, dim3(256), 0, st, E4, inv, offsets, M, NB, D4, o4); break;
-      case 4: hipLaunchKernelGGL(k_pool4<4>, grid, dim3(256), 0, st, E4, inv, offsets, M, NB, D4, o4); break;
-      case 8: hipLaunchKernelGGL(k_pool4<8>, grid, dim3(256), 0, st, E4, inv, offsets, M, NB, D4, o4); break;
-      case 16: hipLaunchKernelGGL(k_pool4<16>, grid, dim3(256), 0, st, E4, inv, offsets, M, NB, D4, o4); break;
-      case 32: hipLaunchKernelGGL(k_pool4<32>, grid, dim3(256), 0, st, E4, inv, offsets, M, NB, D4, o4); break;
-      default: hipLaunchKernelGGL(k_pool4<64>, grid, dim3(256), 0, st, E4, inv, offsets, M, NB, D4, o4); break;
+      case 1: hipLaunchKernelGGL(k_pool4<1>, grid, dim3(256), 0, st, E4, inv, offsets, M, NB, D4, o4, ctr); break;
+      case 2: hipLaunchKernelGGL(k_pool4<2>, grid, dim3(256), 0, st, E4, inv, offsets, M, NB, D4, o4, ctr); break;
+      case 4: hipLaunchKernelGGL(k_pool4<4>, grid, dim3(256), 0, st, E4, inv, offsets, M, NB, D4, o4, ctr); break;
+      case 8: hipLaunchKernelGGL(k_pool4<8>, grid, dim3(256), 0, st, E4, inv, offsets, M, NB, D4, o4, ctr); break;
+      case 16: hipLaunchKernelGGL(k_pool4<16>, grid, dim3(256), 0, st, E4, inv, offsets, M, NB, D4, o4, ctr); break;
+      case 32: hipLaunchKernelGGL(k_pool4<32>, grid, dim3(256), 0, st, E4, inv, offsets, M, NB, D4, o4, ctr); break;
+      default: hipLaunchKernelGGL(k_pool4<64>, grid, dim3(256), 0, st, E4, inv, offsets, M, NB, D4, o4, ctr); break;
     }
   } else {
-    hipLaunchKernelGGL(k_pool1, dim3((unsigned)((NB + 3) / 4)), dim3(256), 0, st, E, inv, offsets, M, NB, s.D, out);
+    hipLaunchKernelGGL(k_pool1, dim3((unsigned)((NB + 3) / 4)), dim3(256), 0, st, E, inv, offsets, M, NB, s.D, out, ctr);
   }
   prof_end(prof, K_POOL, st);
   return hipGetLastError();
@@ -945,8 +954,7 @@ hipError_t launch_forward(const Shape& s, const Work& w, const float* G1, const 
                           hipStream_t st) {
   if (M > 0) {
     const int grid = persistent_grid() * 2;
-    hipError_t e = fill_u32(reinterpret_cast<uint32_t*>(w.ctr + C_FWD_CTR), SCHED_NQ * SCHED_STRIDE, 0u, st);
-    if (e != hipSuccess) return e;
+    hipError_t e = hipSuccess;
     if (fwd_r32_supported(s, M)) {
       const int blocks = persistent_grid() * F32_WG_PER_CU;
       prof_begin(prof, K_FWD_FUSED, st);
@@ -957,7 +965,7 @@ hipError_t launch_forward(const Shape& s, const Work& w, const float* G1, const 
       prof_end(prof, K_FWD_FUSED, st);
       e = hipGetLastError();
       if (e != hipSuccess) return e;
-      return launch_pool(s, w.E, w.inv, offsets, M, B, out, prof, st);
+      return launch_pool(s, w.E, w.inv, offsets, M, B, out, w.ctr, prof, st);
     }
     if (fwd_r64_supported(s, M)) {
       const int blocks = persistent_grid() * F64_WG_PER_CU;
@@ -968,11 +976,11 @@ hipError_t launch_forward(const Shape& s, const Work& w, const float* G1, const 
       prof_end(prof, K_FWD_FUSED, st);
       e = hipGetLastError();
       if (e != hipSuccess) return e;
-      return launch_pool(s, w.E, w.inv, offsets, M, B, out, prof, st);
+      return launch_pool(s, w.E, w.inv, offsets, M, B, out, w.ctr, prof, st);
     }
     if (s.sched != SCHED_STEAL_CKPT) {
       if ((e = launch_fwd_any(s, w, G1, G2, G3, prof, st)) != hipSuccess) return e;
-      return launch_pool(s, w.E, w.inv, offsets, M, B, out, prof, st);
+      return launch_pool(s, w.E, w.inv, offsets, M, B, out, w.ctr, prof, st);
     }
     const size_t nC = (size_t)s.d1 * s.d2 * s.R, nA = (size_t)s.d1 * s.R;
     const size_t bs = (size_t)s.R * (s.d2 * s.R + 1);
@@ -1000,7 +1008,7 @@ hipError_t launch_forward(const Shape& s, const Work& w, const float* G1, const 
     e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  return launch_pool(s, w.E, w.inv, offsets, M, B, out, prof, st);
+  return launch_pool(s, w.E, w.inv, offsets, M, B, out, w.ctr, prof, st);
 }
 
 }  // namespace ttemb

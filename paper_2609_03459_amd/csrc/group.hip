@@ -196,8 +196,20 @@ __global__ void k_check_offsets(const int64_t* __restrict__ offsets, int64_t NB,
 // pay more for the waves' digit counts.  4 / 8 / 16 waves: forward of the 8-table workload
 // (5.2M keys, 9-bit passes) 723 / 714 / 724 us, 32,768 single look-ups (8-bit) 100 / 93 / 92.
 constexpr int SORT_WAVES = 8;
-template <int BITS>
-__global__ void __launch_bounds__(256) k_radix_hist(const uint32_t* __restrict__ keys, int n, int shift,
+// What a pass sorts by: the keys themselves, or with G3 the (table, i3) of unique-row keys,
+// t n3 + i3, of which there are ctr[C_U].
+struct SortBy {
+  FastDiv Npad, n3;
+  const int32_t* ctr;
+};
+template <bool G3>
+__device__ __forceinline__ uint32_t sort_key(uint32_t k, const SortBy& by) {
+  if (!G3) return k;
+  const uint32_t t = quot(k, by.Npad), g = k - t * by.Npad.d;
+  return t * by.n3.d + (g - quot(g, by.n3) * by.n3.d);
+}
+template <int BITS, bool G3>
+__global__ void __launch_bounds__(256) k_radix_hist(const uint32_t* __restrict__ keys, int n, int shift, SortBy by,
                                                     uint32_t* __restrict__ counts, int ntiles) {
   constexpr int NB = 1 << BITS, NT = 256, ITEMS = SORT_TILE / NT;
   __shared__ uint32_t h[4][NB];  // one histogram per wave
@@ -206,6 +218,7 @@ __global__ void __launch_bounds__(256) k_radix_hist(const uint32_t* __restrict__
   // on the same XCD
   const int tile = (int)xcd_block(blockIdx.x, gridDim.x);
   if (tile >= ntiles) return;
+  if (G3) n = n < by.ctr[C_U] ? n : by.ctr[C_U];
   const int w = threadIdx.x >> 6;
   for (int k = threadIdx.x; k < 4 * NB; k += NT) (&h[0][0])[k] = 0;
   __syncthreads();
@@ -218,10 +231,10 @@ __global__ void __launch_bounds__(256) k_radix_hist(const uint32_t* __restrict__
     for (int j = 0; j < ITEMS / 4; ++j) v[j] = k4[j * NT];
 #pragma unroll
     for (int j = 0; j < ITEMS / 4; ++j) {
-      atomicAdd(&h[w][(v[j].x >> shift) & (NB - 1)], 1u);
-      atomicAdd(&h[w][(v[j].y >> shift) & (NB - 1)], 1u);
-      atomicAdd(&h[w][(v[j].z >> shift) & (NB - 1)], 1u);
-      atomicAdd(&h[w][(v[j].w >> shift) & (NB - 1)], 1u);
+      atomicAdd(&h[w][(sort_key<G3>(v[j].x, by) >> shift) & (NB - 1)], 1u);
+      atomicAdd(&h[w][(sort_key<G3>(v[j].y, by) >> shift) & (NB - 1)], 1u);
+      atomicAdd(&h[w][(sort_key<G3>(v[j].z, by) >> shift) & (NB - 1)], 1u);
+      atomicAdd(&h[w][(sort_key<G3>(v[j].w, by) >> shift) & (NB - 1)], 1u);
     }
   } else {
     uint32_t k[ITEMS];
@@ -232,7 +245,7 @@ __global__ void __launch_bounds__(256) k_radix_hist(const uint32_t* __restrict__
     }
 #pragma unroll
     for (int j = 0; j < ITEMS; ++j)
-      if (base + j * NT + (int)threadIdx.x < n) atomicAdd(&h[w][(k[j] >> shift) & (NB - 1)], 1u);
+      if (base + j * NT + (int)threadIdx.x < n) atomicAdd(&h[w][(sort_key<G3>(k[j], by) >> shift) & (NB - 1)], 1u);
   }
   __syncthreads();
   for (int d = threadIdx.x; d < NB; d += NT) counts[d * ntiles + tile] = h[0][d] + h[1][d] + h[2][d] + h[3][d];
@@ -274,15 +287,16 @@ __global__ void __launch_bounds__(256) k_radix_scan(uint32_t* __restrict__ count
 // Ranks come from per-wave ballots; the tile is first placed in LDS in digit
 // order, then written out so that consecutive threads of one digit write
 // consecutive addresses.  vin null: the positions are the input order (the first pass of
-// the grouping's sort).  totals null: offs holds the raw tile counts, and the block sums
-// the tiles before its own itself (few tiles: one launch less per pass).
-template <int BITS, int W>
+// the grouping's sort).  few: offs holds the raw tile counts, and the block sums the tiles
+// before its own itself (one launch less per pass).  G3 sorts unique rows by (table, i3):
+// only the row ids are written, and the digit totals are left for their reader.
+template <int BITS, int W, bool G3>
 __global__ void __launch_bounds__(64 * W) k_radix_scatter(const uint32_t* __restrict__ kin,
                                                                 const uint32_t* __restrict__ vin,
                                                                 uint32_t* __restrict__ kout,
-                                                                uint32_t* __restrict__ vout, int n, int shift,
+                                                                uint32_t* __restrict__ vout, int n, int shift, SortBy by,
                                                                 const uint32_t* __restrict__ offs, int ntiles,
-                                                                const uint32_t* __restrict__ totals) {
+                                                                int few, uint32_t* __restrict__ totals) {
   constexpr int NB = 1 << BITS, NT = 64 * W, ITEMS = SORT_TILE / NT;
   __shared__ uint32_t wh[W][NB];  // per-wave digit counts, then the wave's local base per digit
   __shared__ uint32_t dpos[NB];   // output position of the tile's first key of each digit, less
@@ -292,6 +306,7 @@ __global__ void __launch_bounds__(64 * W) k_radix_scatter(const uint32_t* __rest
   // tiles in order, an eighth per XCD (as in the histogram of the same pass)
   const int tile = (int)xcd_block(blockIdx.x, gridDim.x);
   if (tile >= ntiles) return;
+  if (G3) n = n < by.ctr[C_U] ? n : by.ctr[C_U];
   const int w = threadIdx.x >> 6;
   const int lane = lane_id();
   for (int k = threadIdx.x; k < W * NB; k += NT) (&wh[0][0])[k] = 0;
@@ -305,7 +320,7 @@ __global__ void __launch_bounds__(64 * W) k_radix_scatter(const uint32_t* __rest
   for (int j = 0; j < ITEMS; ++j) {
     const int i = base + j * 64 + lane;
     const bool ok = i < n;
-    key[j] = ok ? kin[i] : 0u;
+    key[j] = ok ? sort_key<G3>(kin[i], by) : 0u;
     val[j] = vin ? (ok ? vin[i] : 0u) : (uint32_t)i;
   }
   // this tile's offset within each digit and the pass's digit totals, loaded with the
@@ -317,7 +332,7 @@ __global__ void __launch_bounds__(64 * W) k_radix_scatter(const uint32_t* __rest
     const int d = threadIdx.x * DPT + q;
     toff[q] = gt[q] = 0u;
     if (d >= NB) continue;
-    if (totals) {
+    if (!few) {
       toff[q] = offs[d * ntiles + tile];
       gt[q] = totals[d];
     } else {
@@ -326,6 +341,7 @@ __global__ void __launch_bounds__(64 * W) k_radix_scatter(const uint32_t* __rest
         gt[q] += v;
         if (x < tile) toff[q] += v;
       }
+      if (G3 && tile == 0) totals[d] = gt[q];
     }
   }
 #pragma unroll
@@ -396,7 +412,7 @@ __global__ void __launch_bounds__(64 * W) k_radix_scatter(const uint32_t* __rest
   for (int p = threadIdx.x; p < nt; p += NT) {
     const uint32_t k = sk[p];
     const uint32_t pos = dpos[(k >> shift) & (NB - 1)] + (uint32_t)p;
-    kout[pos] = k;
+    if (!G3) kout[pos] = k;
     vout[pos] = sv[p];
   }
 }
@@ -767,22 +783,61 @@ __global__ void k_dense_set(const int32_t* __restrict__ pg_start, const uint32_t
   }
 }
 
-__global__ void k_make_slices(const uint32_t* __restrict__ dense_cnt, const uint32_t* __restrict__ dense_base,
-                              const int32_t* __restrict__ dense_pg, int64_t ndense,
-                              const int32_t* __restrict__ pg_start, const uint32_t* __restrict__ pg_key, int n1,
-                              int slice_rows, int4* __restrict__ slices, int32_t* __restrict__ slice_i1) {
-  for (int64_t s = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; s < ndense;
-       s += (int64_t)gridDim.x * blockDim.x) {
-    uint32_t c = dense_cnt[s];
+// The exclusive scan of the prefix slots' slice counts and the slices themselves, a tile of
+// SCAN_TILE slots per block: each thread scans DOWN_ITEMS consecutive slots, the slots' first
+// slices go through LDS, and the slices are written slot by slot in lane order.  tsum: the
+// tiles' totals (null: a single tile).
+__global__ void __launch_bounds__(DOWN_THREADS) k_scan_slices(const uint32_t* __restrict__ dense_cnt,
+                                                              const int32_t* __restrict__ dense_pg, int64_t ndense,
+                                                              const uint32_t* __restrict__ tsum,
+                                                              const int32_t* __restrict__ pg_start,
+                                                              const uint32_t* __restrict__ pg_key, FastDiv n1,
+                                                              int slice_rows, uint32_t* __restrict__ dense_base,
+                                                              int4* __restrict__ slices,
+                                                              int32_t* __restrict__ slice_i1,
+                                                              int32_t* __restrict__ ctr) {
+  __shared__ uint32_t base[SCAN_TILE + SCAN_TILE / 32], cnt[SCAN_TILE + SCAN_TILE / 32];
+  __shared__ uint32_t smem[DOWN_THREADS / 64];
+  const int64_t t0 = (int64_t)blockIdx.x * SCAN_TILE;
+#pragma unroll
+  for (int j = 0; j < DOWN_ITEMS; ++j) {
+    const int e = j * DOWN_THREADS + (int)threadIdx.x;
+    cnt[pad32(e)] = t0 + e < ndense ? dense_cnt[t0 + e] : 0u;
+  }
+  __syncthreads();
+  const int e0 = (int)threadIdx.x * DOWN_ITEMS;
+  uint32_t v[DOWN_ITEMS], sum = 0;
+#pragma unroll
+  for (int k = 0; k < DOWN_ITEMS; ++k) {
+    v[k] = cnt[pad32(e0 + k)];
+    sum += v[k];
+  }
+  const uint32_t before = tsum ? block_sum_first<uint32_t, DOWN_THREADS>(tsum, (int)blockIdx.x, smem) : 0u;
+  uint32_t tot;
+  uint32_t acc = block_excl_scan<uint32_t, DOWN_THREADS>(sum, smem, &tot) + before;
+  if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) ctr[C_NSLICES] = (int32_t)(before + tot);
+#pragma unroll
+  for (int k = 0; k < DOWN_ITEMS; ++k) {
+    base[pad32(e0 + k)] = acc;
+    acc += v[k];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < DOWN_ITEMS; ++j) {
+    const int e = j * DOWN_THREADS + (int)threadIdx.x;
+    const int64_t s = t0 + e;
+    if (s >= ndense) continue;
+    const uint32_t b = base[pad32(e)], c = cnt[pad32(e)];
+    dense_base[s] = b;
     if (!c) continue;
-    int p = dense_pg[s];
-    uint32_t b = dense_base[s];
-    int r0 = pg_start[p], r1 = pg_start[p + 1];
+    const int p = dense_pg[s];
+    const int r0 = pg_start[p], r1 = pg_start[p + 1];
+    const int key = (int)pg_key[p];
+    const uint32_t i1 = (uint32_t)s - quot((uint32_t)s, n1) * n1.d;  // slot = (t * n2 + i2) * n1 + i1
     for (uint32_t k = 0; k < c; ++k) {
-      int rb = r0 + (int)k * slice_rows;
-      int re = rb + slice_rows < r1 ? rb + slice_rows : r1;
-      slices[b + k] = make_int4(p, rb, re, (int)pg_key[p]);
-      slice_i1[b + k] = (int)(s % n1);  // slot = (t * n2 + i2) * n1 + i1
+      const int rb = r0 + (int)k * slice_rows;
+      slices[b + k] = make_int4(p, rb, rb + slice_rows < r1 ? rb + slice_rows : r1, key);
+      slice_i1[b + k] = (int)i1;
     }
   }
 }
@@ -881,37 +936,53 @@ __global__ void k_make_group_chunks(const uint32_t* __restrict__ dense_cnt, cons
   }
 }
 
-// k_run_counts and the scan of its counts in one workgroup when nruns + 1 <=
-// SCAN_TILE: chunk counts per run, exclusive scan into run_nch (the total at
-// run_nch[nruns] and in ctr[C_NCHUNKS]).  A thread owns SCAN_ITEMS consecutive
-// runs.
-__global__ void __launch_bounds__(SCAN_THREADS) k_runs_one_block(const uint32_t* __restrict__ dense_base,
-                                                                 int32_t* __restrict__ ctr, int nruns, int n1,
-                                                                 int unit, int most, int target, uint32_t* __restrict__ run_nch) {
-  __shared__ uint32_t smem[SCAN_THREADS / 64];
+// Up to SCAN_TILE - 1 runs: the chunk counts per run, their exclusive scan (into run_nch,
+// the total at run_nch[nruns] and in ctr[C_NCHUNKS]) and the chunk list in one launch.  Every
+// block scans all the runs for itself, each thread RC_ITEMS consecutive ones, and searches
+// its chunks' runs in LDS; the first block writes the scan out.
+constexpr int RC_THREADS = 1024, RC_ITEMS = SCAN_TILE / RC_THREADS;
+__global__ void __launch_bounds__(RC_THREADS) k_run_chunks(const uint32_t* __restrict__ dense_base,
+                                                           int32_t* __restrict__ ctr, int nruns, int n1, int unit,
+                                                           int most, int target, uint32_t* __restrict__ run_nch,
+                                                           int4* __restrict__ chunks) {
+  __shared__ uint32_t first[SCAN_TILE + 1];  // first chunk of each run
+  __shared__ uint32_t smem[RC_THREADS / 64];
   const uint32_t nsl = (uint32_t)ctr[C_NSLICES];
   const uint32_t cs = chunk_len(nsl, unit, most, target);
-  const int r0 = (int)threadIdx.x * SCAN_ITEMS;
-  uint32_t b[SCAN_ITEMS + 1], cnt[SCAN_ITEMS], sum = 0;
+  const int r0 = (int)threadIdx.x * RC_ITEMS;
+  uint32_t b[RC_ITEMS + 1], cnt[RC_ITEMS], sum = 0;
 #pragma unroll
-  for (int k = 0; k <= SCAN_ITEMS; ++k) {
-    const int r = r0 + k;
-    b[k] = r < nruns ? dense_base[(int64_t)r * n1] : nsl;
-  }
+  for (int k = 0; k <= RC_ITEMS; ++k) b[k] = r0 + k < nruns ? dense_base[(int64_t)(r0 + k) * n1] : nsl;
 #pragma unroll
-  for (int k = 0; k < SCAN_ITEMS; ++k) {
+  for (int k = 0; k < RC_ITEMS; ++k) {
     cnt[k] = r0 + k < nruns ? (b[k + 1] - b[k] + cs - 1) / cs : 0u;
     sum += cnt[k];
   }
-  uint32_t tot;
-  uint32_t acc = block_excl_scan<uint32_t, SCAN_THREADS>(sum, smem, &tot);
+  uint32_t nch;
+  uint32_t acc = block_excl_scan<uint32_t, RC_THREADS>(sum, smem, &nch);
 #pragma unroll
-  for (int k = 0; k < SCAN_ITEMS; ++k) {
-    const int r = r0 + k;
-    if (r <= nruns) run_nch[r] = acc;
+  for (int k = 0; k < RC_ITEMS; ++k) {
+    if (r0 + k <= nruns) {
+      first[r0 + k] = acc;
+      if (blockIdx.x == 0) run_nch[r0 + k] = acc;
+    }
     acc += cnt[k];
   }
-  if (threadIdx.x == 0) ctr[C_NCHUNKS] = (int32_t)tot;
+  if (blockIdx.x == 0 && threadIdx.x == 0) ctr[C_NCHUNKS] = (int32_t)nch;
+  __syncthreads();
+  for (uint32_t c = blockIdx.x * RC_THREADS + threadIdx.x; c < nch; c += gridDim.x * RC_THREADS) {
+    int lo = 0, hi = nruns;  // the last run whose first chunk does not come after c (never an empty one)
+    while (hi - lo > 1) {
+      const int mid = (lo + hi) >> 1;
+      if (first[mid] <= c)
+        lo = mid;
+      else
+        hi = mid;
+    }
+    const uint32_t b1 = lo + 1 < nruns ? dense_base[(int64_t)(lo + 1) * n1] : nsl;
+    const uint32_t f = dense_base[(int64_t)lo * n1] + (c - first[lo]) * cs;
+    chunks[c] = make_int4((int)f, (int)(b1 - f < cs ? b1 - f : cs), lo, 0);
+  }
 }
 
 // Clears what a grouping accumulates into: the counters and the error word, the
@@ -947,13 +1018,39 @@ static hipError_t radix_pass(const Work& w, int cur, int n, int shift, int ntile
                              bool first = false) {
   constexpr int W = SORT_WAVES;
   if (!first)
-    hipLaunchKernelGGL(k_radix_hist<BITS>, dim3(xcd_grid(ntiles)), dim3(256), 0, st, w.keys[cur], n, shift, w.rcounts,
-                       ntiles);
+    hipLaunchKernelGGL((k_radix_hist<BITS, false>), dim3(xcd_grid(ntiles)), dim3(256), 0, st, w.keys[cur], n, shift,
+                       SortBy(), w.rcounts, ntiles);
   const bool few = ntiles <= FEW_TILES;
   if (!few) hipLaunchKernelGGL(k_radix_scan, dim3(1 << BITS), dim3(256), 0, st, w.rcounts, ntiles, tot);
-  hipLaunchKernelGGL((k_radix_scatter<BITS, W>), dim3(xcd_grid(ntiles)), dim3(64 * W), 0, st, w.keys[cur],
+  hipLaunchKernelGGL((k_radix_scatter<BITS, W, false>), dim3(xcd_grid(ntiles)), dim3(64 * W), 0, st, w.keys[cur],
                      first ? (const uint32_t*)nullptr : w.vals[cur], w.keys[cur ^ 1], w.vals[cur ^ 1], n, shift,
-                     (const uint32_t*)w.rcounts, ntiles, few ? (const uint32_t*)nullptr : (const uint32_t*)tot);
+                     SortBy(), (const uint32_t*)w.rcounts, ntiles, few ? 1 : 0, tot);
+  return hipGetLastError();
+}
+// One pass by (table, i3) over the unique rows (n bounds their number), row ids into rows and
+// the rows per bin into totals.
+template <int BITS>
+static void g3_pass(const Shape& s, const Work& w, int n, uint32_t* rows, hipStream_t st) {
+  constexpr int W = SORT_WAVES;
+  const int ntiles = (n + SORT_TILE - 1) / SORT_TILE;
+  const SortBy by = {fast_div_of(s.Npad), fast_div_of((uint32_t)s.n3), w.ctr};
+  const bool few = ntiles <= FEW_TILES;
+  hipLaunchKernelGGL((k_radix_hist<BITS, true>), dim3(xcd_grid(ntiles)), dim3(256), 0, st, (const uint32_t*)w.uniq_key,
+                     n, 0, by, w.rcounts, ntiles);
+  if (!few) hipLaunchKernelGGL(k_radix_scan, dim3(1 << BITS), dim3(256), 0, st, w.rcounts, ntiles, w.rtotals);
+  hipLaunchKernelGGL((k_radix_scatter<BITS, W, true>), dim3(xcd_grid(ntiles)), dim3(64 * W), 0, st,
+                     (const uint32_t*)w.uniq_key, (const uint32_t*)nullptr, (uint32_t*)nullptr, rows, n, 0, by,
+                     (const uint32_t*)w.rcounts, ntiles, few ? 1 : 0, w.rtotals);
+}
+hipError_t sort_rows_by_i3(const Shape& s, const Work& w, int n, uint32_t* rows, hipStream_t st) {
+  int bits = 8;
+  while ((1 << bits) < s.T * s.n3) ++bits;
+  switch (bits) {
+    case 8: g3_pass<8>(s, w, n, rows, st); break;
+    case 9: g3_pass<9>(s, w, n, rows, st); break;
+    case 10: g3_pass<10>(s, w, n, rows, st); break;
+    default: g3_pass<11>(s, w, n, rows, st); break;
+  }
   return hipGetLastError();
 }
 template <int BITS>
@@ -1071,18 +1168,23 @@ hipError_t launch_group(const Shape& s, const Work& w, const int64_t* idx, int64
   hipLaunchKernelGGL(k_dense_set, dim3(grid_for(M, 256, 2048)), dim3(256), 0, st, (const int32_t*)w.pg_start,
                      (const uint32_t*)w.pg_key, (const int32_t*)w.ctr, s.n1, s.n2, s.slice_rows, w.dense_cnt,
                      w.dense_pg);
-  e = scan_generic<uint32_t, false>(w.dense_cnt, w.dense_base, s.ndense, w.tsum32, w.ctr + C_NSLICES, st);
-  if (e != hipSuccess) return e;
-  if (s.slice_rows == 1)
+  if (s.slice_rows == 1) {
+    e = scan_generic<uint32_t, false>(w.dense_cnt, w.dense_base, s.ndense, w.tsum32, w.ctr + C_NSLICES, st);
+    if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_make_slices_rows, dim3(grid_for(M, 256, 8192)), dim3(256), 0, st,
                        (const uint32_t*)w.dense_base, (const int32_t*)w.dense_pg,
                        s.ndense, (const int32_t*)w.pg_start, (const uint32_t*)w.pg_key, s.n1, (const int32_t*)w.ctr,
                        w.slices, w.slice_i1);
-  else
-    hipLaunchKernelGGL(k_make_slices, dim3(grid_for(s.ndense, 256, 4096)), dim3(256), 0, st,
-                       (const uint32_t*)w.dense_cnt, (const uint32_t*)w.dense_base, (const int32_t*)w.dense_pg,
-                       s.ndense, (const int32_t*)w.pg_start, (const uint32_t*)w.pg_key, s.n1, s.slice_rows,
-                       w.slices, w.slice_i1);
+  } else {
+    const int dt = (int)((s.ndense + SCAN_TILE - 1) / SCAN_TILE);
+    if (dt > 1)
+      hipLaunchKernelGGL(k_scan_reduce<uint32_t>, dim3(dt), dim3(SCAN_THREADS), 0, st, (const uint32_t*)w.dense_cnt,
+                         s.ndense, w.tsum32);
+    hipLaunchKernelGGL(k_scan_slices, dim3(dt), dim3(DOWN_THREADS), 0, st, (const uint32_t*)w.dense_cnt,
+                       (const int32_t*)w.dense_pg, s.ndense, dt > 1 ? (const uint32_t*)w.tsum32 : nullptr,
+                       (const int32_t*)w.pg_start, (const uint32_t*)w.pg_key, fast_div_of(s.n1), s.slice_rows,
+                       w.dense_base, w.slices, w.slice_i1, w.ctr);
+  }
   const int nruns = s.T * s.n2;
   if (s.sched == SCHED_GROUP) {
     // slot chunk counts, then their exclusive scan, in dense_pg (free once the slices are made)
@@ -1099,15 +1201,16 @@ hipError_t launch_group(const Shape& s, const Work& w, const int64_t* idx, int64
     return hipGetLastError();
   }
   if (nruns + 1 <= SCAN_TILE) {
-    hipLaunchKernelGGL(k_runs_one_block, dim3(1), dim3(SCAN_THREADS), 0, st, (const uint32_t*)w.dense_base, w.ctr,
-                       nruns, s.n1, s.chunk_unit, s.chunk_slices, s.chunk_target, w.run_nch);
-  } else {
-    hipLaunchKernelGGL(k_run_counts, dim3((nruns + 1 + 255) / 256), dim3(256), 0, st, (const uint32_t*)w.dense_base,
-                       (const int32_t*)w.ctr, nruns, s.n1, s.chunk_unit, s.chunk_slices, s.chunk_target, w.run_nch);
-    // exclusive scan in place; the tile sums buffer of the dense scan is free again
-    e = scan_generic<uint32_t, false>(w.run_nch, w.run_nch, nruns + 1, w.tsum32, w.ctr + C_NCHUNKS, st);
-    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_run_chunks, dim3(grid_for(w.nch_max, RC_THREADS, 64)), dim3(RC_THREADS), 0, st,
+                       (const uint32_t*)w.dense_base, w.ctr, nruns, s.n1, s.chunk_unit, s.chunk_slices, s.chunk_target,
+                       w.run_nch, w.chunks);
+    return hipGetLastError();
   }
+  hipLaunchKernelGGL(k_run_counts, dim3((nruns + 1 + 255) / 256), dim3(256), 0, st, (const uint32_t*)w.dense_base,
+                     (const int32_t*)w.ctr, nruns, s.n1, s.chunk_unit, s.chunk_slices, s.chunk_target, w.run_nch);
+  // exclusive scan in place; the tile sums buffer of the dense scan is free again
+  e = scan_generic<uint32_t, false>(w.run_nch, w.run_nch, nruns + 1, w.tsum32, w.ctr + C_NCHUNKS, st);
+  if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_make_chunks, dim3(grid_for(w.nch_max, 256, 1024)), dim3(256), 0, st,
                      (const uint32_t*)w.dense_base, (const uint32_t*)w.run_nch, (const int32_t*)w.ctr, nruns, s.n1,
                      s.chunk_unit, s.chunk_slices, s.chunk_target, w.chunks);

@@ -573,7 +573,8 @@ tt_emb_status tt_emb_forward_n(tt_emb_handle h, const float* const* cores, const
   const float *G1 = cores[0], *G2 = cores[1], *G3 = cores[L - 1];
   hipError_t e = hipSuccess;
   if (L == 2) {
-    e = launch_identity(h->s, w, s);
+    // only the checkpointed kernels multiply by the identity
+    if (h->s.sched == SCHED_STEAL_CKPT) e = launch_identity(h->s, w, s);
     G2 = w.g1m;
   } else if (L >= 4) {
     e = launch_merge(h->s, w, cores, h->prof, s);
@@ -603,7 +604,7 @@ tt_emb_status tt_emb_backward_n(tt_emb_handle h, const float* const* cores, cons
   float *dG1 = grads[0], *dG2 = grads[1], *dG3 = grads[L - 1];
   hipError_t e = hipSuccess;
   if (L == 2) {
-    e = launch_identity(h->s, w, s);
+    if (h->s.sched == SCHED_STEAL_CKPT) e = launch_identity(h->s, w, s);
     G2 = w.g1m;
     dG2 = w.dg1m;
   } else if (L >= 4) {

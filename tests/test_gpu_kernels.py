@@ -116,3 +116,27 @@ def test_grouping_bag_and_tile_edges(lib, orc, bags, filled):
     got, ref = emb.debug_grouping(case["idx"].size), orc.grouping(case)
     for k in ("inv", "occ_start", "occ_pos", "pg_start"):
         assert np.array_equal(got[k], ref[k]), k
+
+
+# rows ordered by (table, i3) in one radix pass up to 2,048 bins, and by a sort past them
+@pytest.mark.parametrize("T,n3", [(1, 200), (2, 1024), (1, 2049), (3, 700)])
+def test_dg3_bins(lib, orc, T, n3):
+    case = ttgen.tiny(8600 + n3, T, (5, 4, n3), (2, 4, 3), 9, B=3000, max_len=3)
+    _check(lib, orc, case, f"T={T} n3={n3}")
+
+
+@pytest.mark.parametrize("d,R", [((4, 4, 8), 32), ((4, 4, 8), 64), ((4, 4, 4), 16)])
+def test_calls_that_reuse_a_grouping(lib, orc, d, R):
+    # the claim counters are zero again after every call on one grouping
+    case = ttgen.tiny(8700 + R, 2, (30, 40, 20), d, R, B=3000, max_len=6)
+    G = [torch.from_numpy(np.ascontiguousarray(case[k])).cuda() for k in ("G1", "G2", "G3")]
+    idx, off = torch.from_numpy(case["idx"]).cuda(), torch.from_numpy(case["offsets"]).cuda()
+    dV = torch.from_numpy(case["dV"]).cuda()
+    emb = lib.TTEmbedding(2, case["N"], case["n"], d, R, max_indices=idx.numel(), max_bags=3000)
+    first = emb.forward(*G, idx, off)
+    ref, mag = orc.backward(case)[:3], orc.backward(abs_case(case))[:3]
+    for _ in range(3):
+        assert torch.equal(emb.forward(*G, idx, off, reuse_grouping=True), first)
+        grads = emb.backward(*G, idx, off, dV, reuse_grouping=True)
+        for k in range(3):
+            assert_close(f"dG{k + 1} {d} R={R}", grads[k].cpu().numpy(), ref[k], mag[k])
