@@ -612,22 +612,23 @@ __global__ void __launch_bounds__(256, KC == 1 ? 4 : (KC == 2 ? 3 : 2)) k_bwd_an
 
 // dG2[t][i2] (R x d2 R) = sum over the slices of run (t, i2), in slice order, of A^T . dC,
 // A = G1[t][i1 of the slice] (d1 x R) and dC the slice's partial (d1 x d2 R): a product
-// contracted over (slice, j1).  Block (run, y): its sixteen waves take cw tiles of 16 of
-// the d2 R columns times 16 / cw parts of the contraction, each with all rows a in KC
-// accumulators, and the parts are added in order through LDS (the same bits run to run).
-// Splitting the contraction is what fills the waves at small d2 R, where a run has one to
-// four column tiles but hundreds of slices.  With `update`, dG2 is G2 and receives
-// G2 - lr sum; G1 must not have been updated yet.
+// contracted over (slice, j1).  Block (run, y): a wave takes 16 CT columns with all rows a
+// (KC x CT accumulator tiles) over a part of the contraction, and the parts are added pair by
+// pair through LDS (the same bits run to run).  Splitting the contraction is what fills the
+// waves at small d2 R, where a run has one to four column tiles but hundreds of slices.  With
+// CT = 4 (d2 R a multiple of 4) a lane's columns are consecutive, one 16-byte load of dC for
+// four products: 73 -> 40 us at d = (4, 4, 4), R = 16, 150k slices.  With `update`, dG2 is G2 and
+// receives G2 - lr sum; G1 must not have been updated yet.
 constexpr int DGA_WAVES = 16;
 constexpr int DGA_STEPS = 4;  // contraction steps whose loads are in flight together
-template <int KC>
+template <int KC, int CT>
 __global__ void __launch_bounds__(64 * DGA_WAVES) k_dg2_any(AnyArgs s, int cw, const float* __restrict__ G1,
                                                             const uint32_t* __restrict__ dense_base,
                                                             const int32_t* __restrict__ slice_i1,
                                                             const int32_t* __restrict__ ctr,
                                                             const float* __restrict__ dCpart,
                                                             float* __restrict__ dG2, float lr, bool update) {
-  __shared__ float red[DGA_WAVES][4 * KC][64];
+  extern __shared__ float red[];  // [DGA_WAVES / 2][4 KC CT][64]
   const int run = blockIdx.x, t = run / s.n2;
   const int lane = lane_id(), w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int l15 = lane & 15, l4 = lane >> 4;
@@ -638,18 +639,20 @@ __global__ void __launch_bounds__(64 * DGA_WAVES) k_dg2_any(AnyArgs s, int cw, c
   const int64_t nk = (int64_t)(hi - lo) * s.d1;  // contraction rows (slice, j1)
   const int64_t nsteps = (nk + 3) / 4;
   const int64_t k0 = nsteps * part / parts, k1 = nsteps * (part + 1) / parts;
-  const int col = 16 * (blockIdx.y * cw + ct) + l15;
-  const int colc = col < s.d2R ? col : s.d2R - 1;
-  f32x4 acc[KC];
+  const int col = CT * (16 * (int)(blockIdx.y * cw + ct) + l15);  // this lane's first column
+  const int colc = col < s.d2R ? col : s.d2R - CT;
+  f32x4 acc[KC][CT];
 #pragma unroll
-  for (int c = 0; c < KC; ++c) acc[c] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int c = 0; c < KC; ++c)
+#pragma unroll
+    for (int q = 0; q < CT; ++q) acc[c][q] = f32x4{0.f, 0.f, 0.f, 0.f};
   const float* G1t = G1 + (int64_t)t * s.n1 * s.d1 * s.R;
   const float* dCr = dCpart + (int64_t)lo * s.d1 * s.d2R + colc;
   // this lane's contraction row 4 step + l4 as (slice, j1), kept by increments
   int64_t sl = (4 * k0 + l4) / s.d1;
   int j1 = (int)(4 * k0 + l4 - sl * s.d1);
   for (int64_t step = k0; step < k1; step += DGA_STEPS) {
-    float a[DGA_STEPS][KC], b[DGA_STEPS];
+    float a[DGA_STEPS][KC], b[DGA_STEPS][CT];
     bool ok[DGA_STEPS];
 #pragma unroll
     for (int u = 0; u < DGA_STEPS; ++u) {
@@ -659,7 +662,14 @@ __global__ void __launch_bounds__(64 * DGA_WAVES) k_dg2_any(AnyArgs s, int cw, c
       const float* Ar = G1t + ((int64_t)i1 * s.d1 + j1) * s.R;
 #pragma unroll
       for (int c = 0; c < KC; ++c) a[u][c] = Ar[16 * c + l15 < s.R ? 16 * c + l15 : s.R - 1];
-      b[u] = ntl(dCr + (ok[u] ? kk : 0) * s.d2R);
+      const float* p = dCr + (ok[u] ? kk : 0) * s.d2R;
+      if (CT == 4) {
+        const f32x4 v = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(p));
+#pragma unroll
+        for (int q = 0; q < CT; ++q) b[u][q] = v[q];
+      } else {
+        b[u][0] = ntl(p);
+      }
       j1 += 4;
       while (j1 >= s.d1) {
         j1 -= s.d1;
@@ -669,18 +679,38 @@ __global__ void __launch_bounds__(64 * DGA_WAVES) k_dg2_any(AnyArgs s, int cw, c
 #pragma unroll
     for (int u = 0; u < DGA_STEPS; ++u)
 #pragma unroll
+      for (int c = 0; c < KC; ++c) {
+        const float av = ok[u] ? a[u][c] : 0.f;
+#pragma unroll
+        for (int q = 0; q < CT; ++q)
+          acc[c][q] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, ok[u] ? b[u][q] : 0.f, acc[c][q], 0, 0, 0);
+      }
+  }
+  // parts p and p + h are added for h = parts / 2, ..., 1
+  float* mine = red + (w % (DGA_WAVES / 2)) * (4 * KC * CT * 64) + lane;
+  for (int h = parts / 2; h > 0; h /= 2) {
+    __syncthreads();
+    // waves of parts h .. 2 h - 1 are waves h cw .. 2 h cw - 1 of the block
+    if (part >= h && part < 2 * h) {
+      float* dst = red + (w - h * cw) * (4 * KC * CT * 64) + lane;
+#pragma unroll
       for (int c = 0; c < KC; ++c)
-        acc[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(ok[u] ? a[u][c] : 0.f, ok[u] ? b[u] : 0.f, acc[c], 0, 0, 0);
-  }
-  if (part > 0) {
 #pragma unroll
-    for (int c = 0; c < KC; ++c)
+        for (int q = 0; q < CT; ++q)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) red[w][4 * c + r][lane] = acc[c][r];
+          for (int r = 0; r < 4; ++r) dst[(4 * (c * CT + q) + r) * 64] = acc[c][q][r];
+    }
+    __syncthreads();
+    if (part < h)
+#pragma unroll
+      for (int c = 0; c < KC; ++c)
+#pragma unroll
+        for (int q = 0; q < CT; ++q)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) acc[c][q][r] += mine[(4 * (c * CT + q) + r) * 64];
   }
-  __syncthreads();
   if (part == 0 && col < s.d2R) {
-    // lane holds dG2[a = 16 c + 4 l4 + r][col]
+    // lane holds dG2[a = 16 c + 4 l4 + r][col + q]
     float* out = dG2 + (int64_t)run * s.R * s.d2R + col;
 #pragma unroll
     for (int c = 0; c < KC; ++c)
@@ -688,10 +718,9 @@ __global__ void __launch_bounds__(64 * DGA_WAVES) k_dg2_any(AnyArgs s, int cw, c
       for (int r = 0; r < 4; ++r) {
         const int a = 16 * c + 4 * l4 + r;
         if (a >= s.R) continue;
-        float v = acc[c][r];
-        for (int p = 1; p < parts; ++p) v += red[w + p * cw][4 * c + r][lane];
         float* o = out + a * s.d2R;
-        *o = update ? *o - lr * v : v;
+#pragma unroll
+        for (int q = 0; q < CT; ++q) o[q] = update ? o[q] - lr * acc[c][q][r] : acc[c][q][r];
       }
   }
 }
@@ -787,15 +816,23 @@ hipError_t launch_bwd_any(const Shape& s, const Work& w, const float* G1, const 
 
 hipError_t launch_dg2_any(const Shape& s, const Work& w, const float* G1, float* dG2, float lr, bool update,
                           hipStream_t st) {
-  const AnyArgs a = any_args(s);
-  const int nt = (a.d2R + 15) / 16;
+  AnyArgs a = any_args(s);
+  const bool four = a.d2R % 4 == 0 && a.d2R >= 32;  // 16-byte columns, at least half of a wave's 64 in use
+  const int nt = (a.d2R + (four ? 63 : 15)) / (four ? 64 : 16);
   int cw = 1;
   while (cw < nt && cw < DGA_WAVES) cw *= 2;
-  const dim3 grid(s.T * s.n2, (nt + cw - 1) / cw);
-  auto fn = s.R <= 16 ? k_dg2_any<1> : (s.R <= 32 ? k_dg2_any<2> : k_dg2_any<4>);
-  hipLaunchKernelGGL(fn, grid, dim3(64 * DGA_WAVES), 0, st, a, cw, G1, (const uint32_t*)w.dense_base,
-                     (const int32_t*)w.slice_i1, (const int32_t*)w.ctr, (const float*)w.dCpart, dG2, lr, update);
-  return hipGetLastError();
+  const int kc = s.R <= 16 ? 1 : (s.R <= 32 ? 2 : 4);
+  const void* fn = four ? (kc == 1 ? (const void*)k_dg2_any<1, 4> : (kc == 2 ? (const void*)k_dg2_any<2, 4> : (const void*)k_dg2_any<4, 4>))
+                        : (kc == 1 ? (const void*)k_dg2_any<1, 1> : (kc == 2 ? (const void*)k_dg2_any<2, 1> : (const void*)k_dg2_any<4, 1>));
+  const size_t lds = sizeof(float) * (DGA_WAVES / 2) * 4 * kc * (four ? 4 : 1) * 64;
+  hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  if (e != hipSuccess) return e;
+  const uint32_t* db = w.dense_base;
+  const int32_t *i1 = w.slice_i1, *ctr = w.ctr;
+  const float* dC = w.dCpart;
+  void* args[] = {&a, &cw, &G1, &db, &i1, &ctr, &dC, &dG2, &lr, &update};
+  e = hipLaunchKernel(fn, dim3(s.T * s.n2, (nt + cw - 1) / cw), dim3(64 * DGA_WAVES), args, lds, st);
+  return e != hipSuccess ? e : hipGetLastError();
 }
 
 }  // namespace ttemb

@@ -282,24 +282,24 @@ __global__ void __launch_bounds__(64 * DG2_WAVES, 8) k_dg2_r64(ShapeArgs s, cons
   const int hi = run + 1 < s.T * s.n2 ? (int)dense_base[slot0 + s.n1] : ctr[C_NSLICES];
   const int n = hi - lo;
   const int k0 = lo + (int)(((int64_t)n * ks) / 2), k1 = lo + (int)(((int64_t)n * (ks + 1)) / 2);
-  f32x4 acc[8];  // tile (mt, nt) -> 2 mt + nt: rows a = 16 mt + .., columns 32 cg + 16 nt + ..
+  f32x4 acc[8];  // tile (m, q) -> 2 m + q: rows a = 4 (row of the tile) + m, columns 32 cg + 2 (column) + q
 #pragma unroll
   for (int k = 0; k < 8; ++k) acc[k] = f32x4{0.f, 0.f, 0.f, 0.f};
   const float* G1t = G1 + (size_t)t * s.n1 * 256;
   // the half's slices 64 at a time, their i1 in the lanes (one load); per slice the
-  // operands A^T[a = 16 mt + l15][j1 = l4] and dC[j1 = l4][32 cg + 16 nt + l15]
+  // operands A^T[a = 4 l15 + m][j1 = l4] and dC[j1 = l4][32 cg + 2 l15 + q], one 16-byte and
+  // one 8-byte load (with tiles of consecutive rows and columns, six 4-byte
+  // loads and 10 us more of the hot-prefix training step's 150)
   for (int base = k0; base < k1; base += 64) {
     const int cnt = k1 - base < 64 ? k1 - base : 64;
     const int my_i1 = slice_i1[base + (lane < cnt ? lane : 0)];
     for (int k = 0; k < cnt; ++k) {
       const int sl = base + k;
-      const float* Ar = G1t + (size_t)__builtin_amdgcn_readlane(my_i1, k) * 256 + l4 * 64 + l15;
-      const float* Cr = dCpart + (size_t)sl * 1024 + l4 * 256 + cg * 32 + l15;
-      float a[4], b[2];
-#pragma unroll
-      for (int m = 0; m < 4; ++m) a[m] = Ar[16 * m];
-#pragma unroll
-      for (int q = 0; q < 2; ++q) b[q] = ntl(Cr + 16 * q);
+      const float* Ar = G1t + (size_t)__builtin_amdgcn_readlane(my_i1, k) * 256 + l4 * 64 + 4 * l15;
+      const float* Cr = dCpart + (size_t)sl * 1024 + l4 * 256 + cg * 32 + 2 * l15;
+      const f32x4 a = *reinterpret_cast<const f32x4*>(Ar);
+      const float2 b2 = ntl2(reinterpret_cast<const float2*>(Cr));
+      const float b[2] = {b2.x, b2.y};
 #pragma unroll
       for (int m = 0; m < 4; ++m)
 #pragma unroll
@@ -316,18 +316,23 @@ __global__ void __launch_bounds__(64 * DG2_WAVES, 8) k_dg2_r64(ShapeArgs s, cons
   }
   __syncthreads();
   if (ks == 0) {
-    // lane holds dG2[a = 16 mt + 4 l4 + r][(j2, b) = 32 cg + 16 nt + l15]
-    float* out = dG2 + (size_t)run * 16384 + cg * 32 + l15;
+    // lane holds dG2[a = 16 l4 + 4 r + m][(j2, b) = 32 cg + 2 l15 + q]
+    float* out = dG2 + (size_t)run * 16384 + cg * 32 + 2 * l15;
 #pragma unroll
     for (int m = 0; m < 4; ++m)
 #pragma unroll
-      for (int q = 0; q < 2; ++q)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const float v = acc[2 * m + q][r] + rq[(4 * (2 * m + q) + r) * 64];
-          float* p = out + (16 * m + 4 * l4 + r) * 256 + 16 * q;
-          *p = update ? *p - lr * v : v;
+      for (int r = 0; r < 4; ++r) {
+        float2 v;
+        v.x = acc[2 * m][r] + rq[(4 * (2 * m) + r) * 64];
+        v.y = acc[2 * m + 1][r] + rq[(4 * (2 * m + 1) + r) * 64];
+        float2* p = reinterpret_cast<float2*>(out + (16 * l4 + 4 * r + m) * 256);
+        if (update) {
+          const float2 g = *p;
+          v.x = g.x - lr * v.x;
+          v.y = g.y - lr * v.y;
         }
+        *p = v;
+      }
   }
 }
 
