@@ -21,8 +21,10 @@
 // registers allow, and the next tile's operands in flight while a tile is computed.
 // Against the block-per-slice vector-ALU kernels these replaced (they remain for the
 // checkpointed schedule): d = (4, 4, 4), R = 16, 4 tables, 655k look-ups, forward kernel
-// 470 -> 98 us, backward 1,311 -> 137 us; d = (3, 4, 5), R = 12, 55k look-ups, 83 -> 26 and
-// 247 -> 52 us; two cores, d = (16, 8), R = 32, 328k look-ups, 218 -> 31 and 594 -> 55 us.
+// 470 -> 93 us, backward 1,311 -> 127 us; d = (3, 4, 5), R = 12, 55k look-ups, 83 -> 26 and
+// 247 -> 52 us; two cores, d = (16, 8), R = 32, 328k look-ups, 218 -> 31 and 594 -> 53 us.
+// With two or four tiles in flight the first shape's kernels take 96 to 111 and 134 to 161 us:
+// the registers cost more waves and spills than the loads in flight gain.
 #pragma once
 
 #include "common.h"
@@ -96,7 +98,7 @@ __device__ __forceinline__ f32x4 load4(const float* p, int k, int n) {
 struct Stack {
   int nq;        // slices (wave-uniform)
   int rb, nr, i1;  // per lane: first row, rows, first digit
-  int tile_end;  // per lane: tiles of slices 0 .. lane
+  int tile_end;  // per lane below 16: tiles of slices 0 .. lane (other lanes 0)
   int ntiles;    // of the whole stack (wave-uniform)
 };
 __device__ __forceinline__ void load_stack(Stack& k, const AnyArgs& s, const int4* __restrict__ slices,
@@ -110,8 +112,14 @@ __device__ __forceinline__ void load_stack(Stack& k, const AnyArgs& s, const int
     k.nr = sd.z - sd.y;
     k.i1 = slice_i1[f + lane];
   }
-  k.tile_end = wave_incl_scan<int>((k.nr * s.d3 + 15) >> 4);
-  k.ntiles = __builtin_amdgcn_readlane(k.tile_end, 63);
+  // inclusive sum over the first 16 lanes, which hold the slices (row shifts by 1, 2, 4, 8)
+  int v = (k.nr * s.d3 + 15) >> 4;
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, true);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, true);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, true);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, true);
+  k.tile_end = v;
+  k.ntiles = __builtin_amdgcn_readlane(v, 15);
 }
 // Slice and first item of tile P (P < ntiles)
 struct TileAt {
@@ -149,6 +157,46 @@ __device__ __forceinline__ void stage1(const AnyArgs& s, const Stack& k, const f
         for (int c = 0; c < KC; ++c)
           if (FULL || 16 * c + 4 * l4 < s.pitch)
             *reinterpret_cast<f32x4*>(scr + (m0 + l15) * s.pitch + 16 * c + 4 * l4) = Aop[c];
+      continue;
+    }
+    if ((FULL || s.R % 4 == 0) && s.d2R >= 32) {
+      // column n0 + 4 l15 + q in tile q: one 16-byte load takes a lane's B words of four
+      // tiles, and its results are four consecutive floats of a C row.  From 32 columns on,
+      // below which half of the lanes would idle; d = (4, 4, 4), R = 16, 4 tables: training
+      // step 491 -> 477 us with it and the places carried between tiles, d = (4, 4, 4) look-up of
+      // one table 88.7 -> 87.2 us.
+      for (int n0 = 0; n0 < s.d2R; n0 += 64) {
+        const int col = n0 + 4 * l15;
+        const float* Bc = B + (col < s.d2R ? col : s.d2R - 4);
+        f32x4 bv[KC][4];
+#pragma unroll
+        for (int c = 0; c < KC; ++c)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const int a = 16 * c + 4 * l4 + i;
+            bv[c][i] = *reinterpret_cast<const f32x4*>(Bc + (FULL || a < s.R ? a : s.R - 1) * s.d2R);
+          }
+        f32x4 acc[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) acc[q] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int c = 0; c < KC; ++c)
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+              const float b = FULL || 16 * c + 4 * l4 + i < s.R ? bv[c][i][q] : 0.f;
+              acc[q] = __builtin_amdgcn_mfma_f32_16x16x4f32(Aop[c][i], b, acc[q], 0, 0, 0);
+            }
+        // lane holds rows m0 + 4 l4 + r of columns col .. col + 3 = (j2, b .. b + 3)
+        const int j2 = (int)fast_div((uint32_t)col, s.mR);
+        float* out = scr + ((m0 + 4 * l4) * s.d2 + j2) * s.pitch + (col - j2 * s.R);
+        if (col < s.d2R)
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            if (m0 + 4 * l4 + r < rows)
+              *reinterpret_cast<f32x4*>(out + r * s.d2 * s.pitch) = f32x4{acc[0][r], acc[1][r], acc[2][r], acc[3][r]};
+      }
       continue;
     }
     for (int n0 = 0; n0 < s.d2R; n0 += 16) {
@@ -225,14 +273,14 @@ __global__ void __launch_bounds__(256, KC == 1 ? 6 : (KC == 2 ? 5 : 3)) k_fwd_an
   };
   Stack k;
   int t = 0;
-  // i3 of this lane's item of tile P, one tile ahead of the G3 loads that need it
-  auto load_i3 = [&](int P) {
-    const TileAt a = tile_at(k, s, P);
+  // a tile's place and i3 of this lane's item of it, one tile ahead of the G3 loads that need them
+  auto load_i3 = [&](TileAt& a, int P) {
+    a = tile_at(k, s, P);
     const int item = a.item0 + l15 < a.nitems ? a.item0 + l15 : a.nitems - 1;
     return uniq_i3[a.rb + (FULL ? item / D3 : (int)fast_div((uint32_t)item, s.md3))];
   };
-  auto load_tile = [&](Tile& X, int P, int i3) {
-    X.at = tile_at(k, s, P);
+  auto load_tile = [&](Tile& X, const TileAt& at, int i3) {
+    X.at = at;
     const int item = X.at.item0 + l15 < X.at.nitems ? X.at.item0 + l15 : X.at.nitems - 1;
     const int j3 = FULL ? item % D3 : item - (int)fast_div((uint32_t)item, s.md3) * d3;
     const float* g = G3 + ((int64_t)t * s.n3 + i3) * (s.R * d3) + j3;
@@ -294,17 +342,18 @@ __global__ void __launch_bounds__(256, KC == 1 ? 6 : (KC == 2 ? 5 : 3)) k_fwd_an
       Tile X, Y;
       // the first tile's operands load while stage 1 runs
       const int last = k.ntiles - 1;
-      int i3a = load_i3(0), i3b = load_i3(last < 1 ? last : 1);
-      load_tile(X, 0, i3a);
+      TileAt ta, tb;
+      int i3a = load_i3(ta, 0), i3b = load_i3(tb, last < 1 ? last : 1);
+      load_tile(X, ta, i3a);
       stage1<KC, FULL>(s, k, G1, B, t, scr);
       wave_lds_sync();
       for (int P = 0; P <= last; P += 2) {
-        i3a = load_i3(P + 2 < last ? P + 2 : last);
-        load_tile(Y, P + 1 < last ? P + 1 : last, i3b);
+        i3a = load_i3(ta, P + 2 < last ? P + 2 : last);
+        load_tile(Y, tb, i3b);
         compute(X);
         if (P + 1 > last) break;
-        i3b = load_i3(P + 3 < last ? P + 3 : last);
-        load_tile(X, P + 2 < last ? P + 2 : last, i3a);
+        i3b = load_i3(tb, P + 3 < last ? P + 3 : last);
+        load_tile(X, ta, i3a);
         compute(Y);
       }
       wave_lds_sync();  // the tile is rewritten by the next stack
@@ -353,8 +402,8 @@ __global__ void __launch_bounds__(256, KC == 1 ? 4 : (KC == 2 ? 3 : 2)) k_bwd_an
   int t = 0;
   auto clamp_item = [&](const TileAt& a, int x) { return a.item0 + x < a.nitems ? a.item0 + x : a.nitems - 1; };
   auto row_of = [&](int item) { return FULL ? item / D3V : (int)fast_div((uint32_t)item, s.md3); };
-  auto load_i3 = [&](int P) {
-    const TileAt a = tile_at(k, s, P);
+  auto load_i3 = [&](TileAt& a, int P) {
+    a = tile_at(k, s, P);
     return uniq_i3[a.rb + row_of(clamp_item(a, l15))];
   };
   auto load_e1 = [&](Tile& X, int jt) {
@@ -507,13 +556,14 @@ __global__ void __launch_bounds__(256, KC == 1 ? 4 : (KC == 2 ? 3 : 2)) k_bwd_an
       const int last = k.ntiles - 1;
       if (FULL || s.rows12 <= 16) {
         Tile X, Y;
-        auto load_tile = [&](Tile& Z, int P, int i3) {
-          Z.at = tile_at(k, s, P);
+        auto load_tile = [&](Tile& Z, const TileAt& at, int i3) {
+          Z.at = at;
           load_e1(Z, 0);
           load_e2g(Z, i3, 0);
         };
-        int i3a = load_i3(0), i3b = load_i3(last < 1 ? last : 1);
-        load_tile(X, 0, i3a);  // loads while stage 1 runs
+        TileAt ta, tb;
+        int i3a = load_i3(ta, 0), i3b = load_i3(tb, last < 1 ? last : 1);
+        load_tile(X, ta, i3a);  // loads while stage 1 runs
         stage1<KC, FULL>(s, k, G1, B, t, scr);
         wave_lds_sync();
         int cj = 0;
@@ -532,12 +582,12 @@ __global__ void __launch_bounds__(256, KC == 1 ? 4 : (KC == 2 ? 3 : 2)) k_bwd_an
           store_dD(Z);
         };
         for (int P = 0; P <= last; P += 2) {
-          i3a = load_i3(P + 2 < last ? P + 2 : last);
-          load_tile(Y, P + 1 < last ? P + 1 : last, i3b);
+          i3a = load_i3(ta, P + 2 < last ? P + 2 : last);
+          load_tile(Y, tb, i3b);
           step(X);
           if (P + 1 > last) break;
-          i3b = load_i3(P + 3 < last ? P + 3 : last);
-          load_tile(X, P + 2 < last ? P + 2 : last, i3a);
+          i3b = load_i3(tb, P + 3 < last ? P + 3 : last);
+          load_tile(X, ta, i3a);
           step(Y);
         }
         store_dC(f + q, cj, 0);
@@ -562,8 +612,8 @@ __global__ void __launch_bounds__(256, KC == 1 ? 4 : (KC == 2 ? 3 : 2)) k_bwd_an
           for (int jt = 0; jt < s.rows12; jt += 16) {
             zero(dC);
             for (int P = P0; P < P1; ++P) {
-              X.at = tile_at(k, s, P);
-              load_e2g(X, load_i3(P), jt);
+              const int i3 = load_i3(X.at, P);
+              load_e2g(X, i3, jt);
               add_dC(X);
             }
             store_dC(f + q, j, jt);
