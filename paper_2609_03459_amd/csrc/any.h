@@ -52,8 +52,23 @@ struct AnyArgs {
   uint32_t mR, md1, md3;  // div_magic of R, d1, d3
 };
 
-// Slices of a stack: their d1 rows of A fill one 16-row tile
-int any_stack_slices(const Shape& s) { return s.d1 >= 16 ? 1 : 16 / s.d1; }
+constexpr size_t ANY_LDS = 160 * 1024 - 1024;
+constexpr size_t ANY_STACK_LDS = ANY_LDS / 4;
+
+static int any_pitch(const Shape& s) { return 4 * (((s.R + 3) / 4) | 1); }
+
+// Slices of a stack: their d1 rows of A fill one 16-row tile, but their C takes at most a
+// quarter of the LDS, so that each SIMD has a wave (up to d1 d2 R = 8192 are accepted, and 16
+// slices of that would take 557 KB; one slice takes 79 KB at most, at R = 5).  With all / a
+// half / a quarter / an eighth of the LDS at most, R = 64, 2 tables, 100k look-ups, training
+// step: d = (2, 16, 4) 2,385 / 2,374 / 2,122 / 2,748 us, d = (1, 32, 4) 4,205 / 3,595 / 3,782 /
+// 5,070 us (block-per-slice kernels: 5,914 and 8,884 us; their forward alone is faster on the
+// second, 1,010 against 1,117 us).
+int any_stack_slices(const Shape& s) {
+  const int fill = s.d1 >= 16 ? 1 : 16 / s.d1;
+  const int fit = (int)(ANY_STACK_LDS / (sizeof(float) * (size_t)(s.d1 * s.d2 * any_pitch(s))));
+  return fit < 1 ? 1 : (fit < fill ? fit : fill);
+}
 
 static AnyArgs any_args(const Shape& s) {
   AnyArgs a;
@@ -71,7 +86,7 @@ static AnyArgs any_args(const Shape& s) {
   a.sq = any_stack_slices(s);
   a.rows12 = s.d1 * s.d2;
   a.d2R = s.d2 * s.R;
-  a.pitch = 4 * (((s.R + 3) / 4) | 1);
+  a.pitch = any_pitch(s);
   a.tile = a.sq * a.rows12 * a.pitch;
   a.mR = div_magic(s.R);
   a.md1 = div_magic(s.d1);
@@ -778,8 +793,6 @@ __global__ void __launch_bounds__(64 * DGA_WAVES) k_dg2_any(AnyArgs s, int cw, c
 // ---------------------------------------------------------------------------
 // launch
 // ---------------------------------------------------------------------------
-constexpr size_t ANY_LDS = 160 * 1024 - 1024;
-
 // Waves per block and blocks per CU: four-wave blocks while their LDS tiles leave room for
 // at least two blocks per CU, else one-wave blocks; at most eight waves per SIMD.
 static void any_grid(const AnyArgs& a, int* waves, int* blocks, size_t* lds) {

@@ -71,6 +71,15 @@ def test_any_shape(lib, orc, d, R, sched):
     _check(lib, orc, case, f"any {d} R={R} {sched}", sched=sched)
 
 
+# a C per prefix near the accepted limit d1 d2 R = 8192, whose stacks hold fewer slices than
+# would fill a tile: 16 slices of the first would take 557 KB of LDS
+@pytest.mark.parametrize("d,R", [((1, 128, 2), 64), ((1, 1024, 2), 8), ((1, 4096, 1), 1), ((2, 64, 2), 64),
+                                 ((3, 546, 1), 5), ((1, 32, 4), 64), ((1, 20, 3), 33)])
+def test_any_shape_large_products(lib, orc, d, R):
+    case = ttgen.tiny(8250 + R, 2, (17, 2, 9), d, R, B=40, max_len=5, sigma=0.3)
+    _check(lib, orc, case, f"any {d} R={R}")
+
+
 @pytest.mark.parametrize("n,d,R", [((40, 30), (16, 8), 32), ((300, 2), (3, 5), 7), ((9, 200), (20, 4), 64)])
 def test_two_cores(lib, orc, n, d, R):
     # the identity middle core is never multiplied: C is A and dA is dC
