@@ -21,10 +21,10 @@
 // registers allow, and the next tile's operands in flight while a tile is computed.
 // Against the block-per-slice vector-ALU kernels these replaced (they remain for the
 // checkpointed schedule): d = (4, 4, 4), R = 16, 4 tables, 655k look-ups, forward kernel
-// 470 -> 93 us, backward 1,311 -> 127 us; d = (3, 4, 5), R = 12, 55k look-ups, 83 -> 26 and
-// 247 -> 52 us; two cores, d = (16, 8), R = 32, 328k look-ups, 218 -> 31 and 594 -> 53 us.
-// With two or four tiles in flight the first shape's kernels take 96 to 111 and 134 to 161 us:
-// the registers cost more waves and spills than the loads in flight gain.
+// 470 -> 97 us, backward 1,311 -> 134 us; d = (3, 4, 5), R = 12, 55k look-ups, 83 -> 25 and
+// 247 -> 45 us; two cores, d = (16, 8), R = 32, 328k look-ups, 218 -> 31 and 594 -> 53 us.
+// With two or four tiles in flight the first shape's kernels took 3 to 20% longer and 6 to 27%
+// longer: the registers cost more waves and spills than the loads in flight gain.
 #pragma once
 
 #include "common.h"
@@ -150,6 +150,19 @@ __device__ __forceinline__ TileAt tile_at(const Stack& k, const AnyArgs& s, int 
   return a;
 }
 
+// A product's terms in four partial sums, added in pairs at the end.  One chain of all terms
+// takes about the same time but rounds more: at R = 16 a row's error against 64 bits is 1.1e-7
+// with it and 7.8e-8 with four, as with the four partial sums of a vector-ALU product.  (Four
+// columns per lane in stage 1, by 16-byte loads, are 2% faster at d = (4, 4, 4) with one chain,
+// 477 against 487 us, but spill with four: 565 us.)
+struct Chains {
+  f32x4 acc[4] = {};
+  __device__ __forceinline__ void mac(int i, float a, float b) {
+    acc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, acc[i], 0, 0, 0);
+  }
+  __device__ __forceinline__ f32x4 sum() const { return (acc[0] + acc[1]) + (acc[2] + acc[3]); }
+};
+
 // Stage 1: C of the stack into the wave's LDS tile.  FULL: R = 16 KC.
 template <int KC, bool FULL>
 __device__ __forceinline__ void stage1(const AnyArgs& s, const Stack& k, const float* __restrict__ G1,
@@ -174,46 +187,6 @@ __device__ __forceinline__ void stage1(const AnyArgs& s, const Stack& k, const f
             *reinterpret_cast<f32x4*>(scr + (m0 + l15) * s.pitch + 16 * c + 4 * l4) = Aop[c];
       continue;
     }
-    if ((FULL || s.R % 4 == 0) && s.d2R >= 32) {
-      // column n0 + 4 l15 + q in tile q: one 16-byte load takes a lane's B words of four
-      // tiles, and its results are four consecutive floats of a C row.  From 32 columns on,
-      // below which half of the lanes would idle; d = (4, 4, 4), R = 16, 4 tables: training
-      // step 491 -> 477 us with it and the places carried between tiles, d = (4, 4, 4) look-up of
-      // one table 88.7 -> 87.2 us.
-      for (int n0 = 0; n0 < s.d2R; n0 += 64) {
-        const int col = n0 + 4 * l15;
-        const float* Bc = B + (col < s.d2R ? col : s.d2R - 4);
-        f32x4 bv[KC][4];
-#pragma unroll
-        for (int c = 0; c < KC; ++c)
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const int a = 16 * c + 4 * l4 + i;
-            bv[c][i] = *reinterpret_cast<const f32x4*>(Bc + (FULL || a < s.R ? a : s.R - 1) * s.d2R);
-          }
-        f32x4 acc[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) acc[q] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int c = 0; c < KC; ++c)
-#pragma unroll
-          for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-              const float b = FULL || 16 * c + 4 * l4 + i < s.R ? bv[c][i][q] : 0.f;
-              acc[q] = __builtin_amdgcn_mfma_f32_16x16x4f32(Aop[c][i], b, acc[q], 0, 0, 0);
-            }
-        // lane holds rows m0 + 4 l4 + r of columns col .. col + 3 = (j2, b .. b + 3)
-        const int j2 = (int)fast_div((uint32_t)col, s.mR);
-        float* out = scr + ((m0 + 4 * l4) * s.d2 + j2) * s.pitch + (col - j2 * s.R);
-        if (col < s.d2R)
-#pragma unroll
-          for (int r = 0; r < 4; ++r)
-            if (m0 + 4 * l4 + r < rows)
-              *reinterpret_cast<f32x4*>(out + r * s.d2 * s.pitch) = f32x4{acc[0][r], acc[1][r], acc[2][r], acc[3][r]};
-      }
-      continue;
-    }
     for (int n0 = 0; n0 < s.d2R; n0 += 16) {
       const int col = n0 + l15;
       const float* Bc = B + (col < s.d2R ? col : s.d2R - 1);
@@ -230,11 +203,12 @@ __device__ __forceinline__ void stage1(const AnyArgs& s, const Stack& k, const f
         for (int c = 0; c < KC; ++c)
 #pragma unroll
           for (int i = 0; i < 4; ++i) bv[c][i] = 16 * c + 4 * l4 + i < s.R ? bv[c][i] : 0.f;
-      f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+      Chains x;
 #pragma unroll
       for (int c = 0; c < KC; ++c)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(Aop[c][i], bv[c][i], acc, 0, 0, 0);
+        for (int i = 0; i < 4; ++i) x.mac(i, Aop[c][i], bv[c][i]);
+      const f32x4 acc = x.sum();
       // lane holds rows m0 + 4 l4 + r of column col = (j2, b)
       const int j2 = (int)fast_div((uint32_t)col, s.mR);
       const int b = col - j2 * s.R;
@@ -317,13 +291,14 @@ __global__ void __launch_bounds__(256, KC == 1 ? 6 : (KC == 2 ? 5 : 3)) k_fwd_an
     for (int jt = 0; jt < (FULL ? 16 : s.rows12); jt += 16) {
       const int jj = jt + l15;
       const float* cr = Cj + (jj < s.rows12 ? jj : s.rows12 - 1) * s.pitch;
-      f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+      Chains x;
 #pragma unroll
       for (int c = 0; c < KC; ++c) {
         const f32x4 ct = load4<FULL>(cr, 16 * c + 4 * l4, s.R);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(X.d[c][i], ct[i], acc, 0, 0, 0);
+        for (int i = 0; i < 4; ++i) x.mac(i, X.d[c][i], ct[i]);
       }
+      const f32x4 acc = x.sum();
       // lane holds items item0 + 4 l4 + r of column jj
       const int it = X.at.item0 + 4 * l4;
       if (jj < s.rows12) {
@@ -642,8 +617,7 @@ __global__ void __launch_bounds__(256, KC == 1 ? 4 : (KC == 2 ? 3 : 2)) k_bwd_an
         const int rows = k.nq * s.d1;
         for (int m0 = 0; m0 < rows; m0 += 16) {
           const int m = m0 + l15 < rows ? m0 + l15 : rows - 1;
-          f32x4 acc[KC];
-          zero(acc);
+          Chains acc[KC];
 #pragma unroll 2
           for (int j2 = 0; j2 < s.d2; ++j2) {
 #pragma unroll
@@ -655,19 +629,20 @@ __global__ void __launch_bounds__(256, KC == 1 ? 4 : (KC == 2 ? 3 : 2)) k_bwd_an
                 const int a = FULL || 16 * at + l15 < s.R ? 16 * at + l15 : s.R - 1;
                 const f32x4 bv = load4<FULL>(B + a * s.d2R + j2 * s.R, b, s.R);
 #pragma unroll
-                for (int i = 0; i < 4; ++i)
-                  acc[at] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[i], bv[i], acc[at], 0, 0, 0);
+                for (int i = 0; i < 4; ++i) acc[at].mac(i, av[i], bv[i]);
               }
             }
           }
           // lane holds dA[stack row m0 + 4 l4 + r][a = 16 at + l15]
           float* out = dApart + (int64_t)(f + q) * s.d1 * s.R;
 #pragma unroll
-          for (int at = 0; at < KC; ++at)
+          for (int at = 0; at < KC; ++at) {
+            const f32x4 dA = acc[at].sum();
 #pragma unroll
             for (int r = 0; r < 4; ++r)
               if (m0 + 4 * l4 + r < rows && (FULL || 16 * at + l15 < s.R))
-                __builtin_nontemporal_store(acc[at][r], out + (m0 + 4 * l4 + r) * s.R + 16 * at + l15);
+                __builtin_nontemporal_store(dA[r], out + (m0 + 4 * l4 + r) * s.R + 16 * at + l15);
+          }
         }
         wave_lds_sync();  // the tile is rewritten by the next stack
       }
