@@ -68,8 +68,8 @@ class HipEvents:
 # of a kernel stay valid while these files are unchanged).
 KERNEL_SOURCES = {
     # the fused kernels' work units (slices, chunks) are cut by the grouping, sized in tt_emb.hip
-    "bwd_fused": ["bwd_r32.hip", "bwd_r64.hip", "common.h", "group.hip", "tt_emb.hip"],
-    "fwd_fused": ["fwd.hip", "common.h", "group.hip", "tt_emb.hip"],
+    "bwd_fused": ["bwd_r32.hip", "bwd_r64.hip", "any.h", "common.h", "group.hip", "tt_emb.hip"],
+    "fwd_fused": ["fwd.hip", "any.h", "common.h", "group.hip", "tt_emb.hip"],
     "pool": ["fwd.hip", "common.h"],
     "seg_sum": ["bwd.hip", "common.h"],
     "ingest": ["group.hip", "common.h"],
@@ -597,7 +597,7 @@ def main():
             phases[name].append(ev.elapsed_ms(pe[j], pe[j + 1]))
     phases_ms = {k: round(float(np.median(v)), 4) for k, v in phases.items()}
 
-    # the fused kernels run on the matrix cores only for the shapes the MFMA kernels serve
+    # a specialised matrix-core kernel's rate is a roofline; the any-shape kernels' tiles are padded
     on_mfma = dominant in ("fwd_fused", "bwd_fused") and P.N.tt_emb_kernel_uses_mfma(
         emb.handle, P.N.KERNELS[dominant], M)
     work, unit, bound = algorithmic_work(dominant, case, counts, on_mfma=bool(on_mfma))

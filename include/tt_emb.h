@@ -124,10 +124,10 @@ tt_emb_status tt_emb_set_reuse(tt_emb_handle h, int level);
  *                            rows, is cut into 64-slice pieces), and each
  *                            worker takes a fixed contiguous share of the
  *                            groups.
- * The checkpoint applies to the kernels that keep one C per worker (the
- * generic kernels); the MFMA kernels (forward and backward for d = (4,4,8)
- * with R = 32 or 64) build C for four slices per matrix-core tile and treat
- * STEAL_CKPT as STEAL.  All
+ * The checkpoint applies to the vector kernels that keep one C per worker,
+ * which serve every shape without a specialised kernel in this mode only; the
+ * specialised MFMA kernels (see tt_emb_kernel_uses_mfma) build C for several
+ * slices per matrix-core tile and treat STEAL_CKPT as STEAL.  All
  * modes compute the same function.  Host only; may be changed between calls,
  * except that TT_EMB_SCHED_GROUP cuts the work list in the grouping and needs a
  * larger workspace: set it before tt_emb_workspace_size, and a grouping made
@@ -203,11 +203,10 @@ tt_emb_status tt_emb_forward_noalloc(tt_emb_handle h, const float* G1, const flo
  * group the dC are summed first and dA = (sum dC) B^T, dB = A^T (sum dC).
  * The per-core gradients are reduced by segments, with no global float
  * atomics: dG1 is a fixed-order sum of per-slice partials over the slices of
- * each (table, i1), dG2 of per-chunk partials over the chunks of each
- * (table, i2), except on the R = 64 MFMA shape, where each slice's sum dC is
- * kept and dG2 of (table, i2) is the product of the stacked A^T and sum dC of
- * its slices, contracted in slice order.  dG3: on the R = 32 MFMA shape (see
- * tt_emb_kernel_uses_mfma)
+ * each (table, i1).  dG2: on the R = 32 MFMA shapes it is a sum of per-chunk
+ * partials over the chunks of each (table, i2); on every other shape each
+ * slice's sum dC is kept and dG2 of (table, i2) is the product of the stacked
+ * A^T and sum dC of its slices, contracted in a fixed order.  dG3: on the R = 32 MFMA shapes (see tt_emb_kernel_uses_mfma)
  * it is summed in on-chip memory per (table, rank half) and workgroup, then
  * over the workgroups in a fixed order (the on-chip adds land in arrival
  * order, so this dG3 is reproducible to rounding, not bit for bit); on every
@@ -334,7 +333,7 @@ typedef enum {
   TT_EMB_K_FWD_FUSED = 2, /* forward: C = A.B per prefix group, E = C.D per unique row */
   TT_EMB_K_POOL = 3,      /* forward: sum pooling of E rows into the bags */
   TT_EMB_K_SEG_SUM = 4,   /* backward: dE per unique row, summed over its occurrences */
-  TT_EMB_K_BWD_FUSED = 5, /* backward: per prefix group dD, dC, sum dC, dA, dB (dB after it at R = 64) */
+  TT_EMB_K_BWD_FUSED = 5, /* backward: per prefix group dD, dC, sum dC, dA, dB (dB after it unless R = 32 and specialised) */
   TT_EMB_K_MERGE = 6,     /* L >= 4: merged first core from cores 0..L-3 */
   TT_EMB_K_SPLIT = 7      /* L >= 4 backward: gradients of cores 0..L-3 from the merged core's */
 } tt_emb_kernel;
@@ -347,12 +346,14 @@ typedef enum {
 tt_emb_status tt_emb_profile(tt_emb_handle h, int kernel, void* ev_begin, void* ev_end);
 
 /* Whether `kernel` (TT_EMB_K_FWD_FUSED or TT_EMB_K_BWD_FUSED) runs on the
- * matrix cores for this handle: *uses_mfma = 1 for the MFMA kernels (forward
+ * specialised matrix-core kernels for this handle: *uses_mfma = 1 for them (forward
  * for the view d = (4,4,8) with R = 32 or 64 and for d = (4,4,2) with R = 32;
  * backward for d = (4,4,8) or (4,4,2) with R = 32, n3 <= 252 and at most 64
  * tables, and for d = (4,4,8) with R = 64; all only while
  * their 32-bit offsets into E and the cores fit and, at R = 64, a table's
- * third core spans under 4 GiB), 0 for the generic vector-ALU kernels.
+ * third core spans under 4 GiB), 0 for the kernels of any shape, whose matrix
+ * tiles are partly padding (and which are vector kernels under
+ * TT_EMB_SCHED_STEAL_CKPT).
  * Both decide per call from its index count, given here as num_indices
  * (0 <= num_indices <= desc.max_indices).  Every other kernel id reports 0.
  * Host only.

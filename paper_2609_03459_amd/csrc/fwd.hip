@@ -42,7 +42,8 @@ __device__ __forceinline__ float fdot_strided(const float* x, int xs, const floa
   return (a0 + a1) + (a2 + a3);
 }
 
-// Generic fused forward for any shape within the library limits (plain VALU).  A
+// Fused forward of the checkpointed schedule for any shape within the library limits, one
+// C per block, on the vector ALU (other schedules: k_fwd_any).  A
 // block claims FWD_CHUNK consecutive slices; B = G2[t][i2] of their (t, i2) run is
 // staged in LDS (rows padded by one float) when it fits, again whenever the run
 // changes; per slice A is staged, C = A.B is built once per prefix group and
@@ -990,11 +991,9 @@ hipError_t launch_forward(const Shape& s, const Work& w, const float* G1, const 
     const void* kfn = wide ? (const void*)k_fwd_generic<1024> : (const void*)k_fwd_generic<256>;
     e = hipFuncSetAttribute(kfn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
-    if (s.sched == SCHED_STEAL_CKPT) {  // checkpoints of earlier calls may hold other cores' C
-      if (!w.ckpt_tag) return hipErrorInvalidValue;
-      e = fill_u32(reinterpret_cast<uint32_t*>(w.ckpt_tag), CKPT_SLOTS, (uint32_t)CKPT_EMPTY, st);
-      if (e != hipSuccess) return e;
-    }
+    if (!w.ckpt_tag) return hipErrorInvalidValue;  // checkpoints of earlier calls may hold other cores' C
+    e = fill_u32(reinterpret_cast<uint32_t*>(w.ckpt_tag), CKPT_SLOTS, (uint32_t)CKPT_EMPTY, st);
+    if (e != hipSuccess) return e;
     prof_begin(prof, K_FWD_FUSED, st);
     if (wide)
       hipLaunchKernelGGL(k_fwd_generic<1024>, dim3(grid), dim3(1024), lds, st, shape_args(s), G1, G2, G3,

@@ -1,6 +1,6 @@
 // Prefix-based index grouping (FlowTT Section 3.3, Fig. 4) on gfx950:
 //   ingest   -> one 32-bit key per occurrence, t*Npad + g (invalid rows get Npad*T)
-//   sort     -> LSD radix sort of (key, position), 8-bit digits, stable
+//   sort     -> LSD radix sort of (key, position), equal digits of up to 11 bits, stable
 //   unique   -> row heads and prefix-group heads, counted per tile and scanned
 //   RLE      -> unique rows, inverse map, occurrence ranges, prefix groups
 //   order    -> prefix groups re-ordered (table, i2, i1) through a dense scan over
